@@ -138,6 +138,10 @@ int tflbm_check_params(const tflbm_params *p);
  * lattice is large enough for it to pay), TFLBM_ROWS, TFLBM_ROWS2,
  * TFLBM_ROWS3, TFLBM_ADJ_ROWS, TFLBM_ADJ_ROWS2 (rows per chunk of the one-,
  * two- and three-step kernels),
+ * TFLBM_BLOCK=0 or n (read at tflbm_init: never the block kernel, or always,
+ * with at most n steps per pass; by default on lattices where it is faster
+ * than the marching kernels, unless one of the variables above asks for a
+ * shape of theirs) and TFLBM_BLOCK_SHAPE (its tile shape),
  * TFLBM_GRAPH=0 or 1 (read at tflbm_init: whether tflbm_step replays blocks
  * of steps from graphs; by default on lattices of at most 2^20 sites). */
 int tflbm_create(const tflbm_params *p, tflbm_sim **out);
@@ -198,10 +202,11 @@ int tflbm_step(tflbm_sim *sim, int64_t nsteps, tflbm_stream_t stream);
  * parity of a block); -1 for NULL. */
 int tflbm_step_graphs(const tflbm_sim *sim);
 
-/* Most time steps one pass of tflbm_step advances on this handle (1, 2 or 3:
- * several steps of eq. "LBE" applied to a row chunk before it is stored; 3
- * needs tau = 1 and a lattice large enough for it to pay; TFLBM_FUSE
- * overrides); EINVAL for NULL, ESTATE before tflbm_init. */
+/* Most time steps one pass of tflbm_step advances on this handle (several
+ * steps of eq. "LBE" applied to a tile before it is stored: up to 8 on
+ * lattices that the block kernel steps; else 1, 2 or 3, of which 3 needs tau = 1
+ * and a lattice large enough for it to pay; TFLBM_FUSE and TFLBM_BLOCK
+ * override); EINVAL for NULL, ESTATE before tflbm_init. */
 int tflbm_steps_per_pass(const tflbm_sim *sim);
 
 /* Number of steps taken since tflbm_init (host counter). */

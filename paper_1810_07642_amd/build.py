@@ -12,11 +12,13 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libtflbm.so")
 # (object, source, defines): the step kernels of each storage form and
-# collision stage are a translation unit of their own (step_form.hip with
-# STEP_FORM and STEP_W1), so that the sources compile in parallel
+# collision stage are a translation unit of their own (step_form.hip and block_form.hip
+# with STEP_FORM and STEP_W1), so that the sources compile in parallel
 UNITS = [(f"step_{form}_{'w1' if w1 else 'general'}", "step_form.hip", [f"-DSTEP_FORM={P}", f"-DSTEP_W1={w1}"])
          for form, P in (("f16s", "kF16S"), ("f32", "kF32"), ("f64", "kF64")) for w1 in (1, 0)]
-UNITS += [(s[:-4], s, []) for s in ("adj.hip", "fwd.hip", "api.hip", "diag.hip", "noalloc.hip")]
+UNITS += [(f"block_{form}_{'w1' if w1 else 'general'}", "block_form.hip", [f"-DSTEP_FORM={P}", f"-DSTEP_W1={w1}"])
+          for form, P in (("f32", "kF32"), ("f64", "kF64")) for w1 in (1, 0)]
+UNITS += [(s[:-4], s, []) for s in ("adj.hip", "fwd.hip", "block.hip", "api.hip", "diag.hip", "noalloc.hip")]
 SOURCES = sorted({src for _, src, _ in UNITS})
 OBJ = os.path.join(PKG, "_build")
 ARCH = "gfx950"

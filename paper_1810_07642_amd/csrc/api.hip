@@ -159,6 +159,10 @@ void plan_launches(tflbm_sim *s) {
   // pass (4096^2: 188.8 vs 284.8 us).
   s->adj_fuse_fits = !(s->w1 && s->p.prec == kF64) &&
                      (int64_t)s->adj_nstrips * ((ny + kMinRowsAdj2 - 1) / kMinRowsAdj2) > (int64_t)aocc2 * cus;
+  // the block kernel, unless a variable asks for a shape of the marching one
+  bool march = s->fuse != 0;
+  for (const char *v : {"TFLBM_ROWS", "TFLBM_ROWS2", "TFLBM_ROWS3"}) march = march || std::getenv(v) != nullptr;
+  if (march || !plan_block(s, s->block)) s->block = BlockPlan();
   s->graphs = (int64_t)s->p.nx * ny <= kGraphMaxSites;
   if (const char *e = std::getenv("TFLBM_GRAPH")) s->graphs = std::atoi(e) != 0;
 }
@@ -367,19 +371,47 @@ int tflbm_init_fields(tflbm_sim *sim, const double *d_h0, const double *d_theta,
   return TFLBM_OK;
 }
 
-// Launches nsteps steps kernel by kernel: passes of the most fused steps the
-// handle allows while that many remain, then shorter ones (with capture: the
-// moments of steps i .. i + ns - 1 of a pass, one capture block apart).
-// Most steps one launch of tflbm_step fuses on this handle.
-static int steps_per_pass(const tflbm_sim *sim) {
-  int ns = sim->fuse != 0 ? sim->fuse : (sim->fuse3_fits ? 3 : (sim->fuse_fits ? 2 : 1));
+// Most steps one launch of the marching kernel fuses on this handle.
+static int march_steps_per_pass(const tflbm_sim *sim) {
+  const int ns = sim->fuse != 0 ? sim->fuse : (sim->fuse3_fits ? 3 : (sim->fuse_fits ? 2 : 1));
   const int nsmax = max_steps_per_pass(sim->p.prec, sim->w1);
   return ns > nsmax ? nsmax : ns;
 }
 
-static int launch_steps(tflbm_sim *sim, int64_t nsteps, void *d_capture, hipStream_t st) {
+// The same by the block kernel: passes of nearly equal length.  Their number is
+// made even or odd with that of the marching kernel's passes, so that a
+// caller's own graph of these steps ends, as before, on the buffer it started
+// from.
+static int launch_block_steps(tflbm_sim *sim, int64_t nsteps, void *d_capture, hipStream_t st) {
+  const int ns_march = march_steps_per_pass(sim);
+  int64_t k = (nsteps + sim->block.ns - 1) / sim->block.ns;
+  if (k < nsteps) k += (k ^ ((nsteps + ns_march - 1) / ns_march)) & 1;
   const size_t cap_bytes = tflbm_capture_bytes(sim);
-  const int ns_max = steps_per_pass(sim);
+  int64_t done = 0;
+  for (int64_t i = 0; i < k; ++i) {
+    const int ns = (int)((nsteps - done + (k - i) - 1) / (k - i));
+    BlockArgs A;
+    A.s = make_step_args(sim);
+    A.s.capture = d_capture ? (char *)d_capture + (size_t)done * cap_bytes : nullptr;
+    shape_block(sim, sim->block.shape, ns, A);
+    A.in_mom = sim->w1 && i > 0;
+    A.out_mom = sim->w1 && i + 1 < k;
+    const int rc = hip_status(sim, launch_block(sim->p.prec, sim->w1, sim->block.shape, A, st));
+    if (rc) return rc;
+    sim->cur ^= 1;
+    sim->steps += ns;
+    done += ns;
+  }
+  return TFLBM_OK;
+}
+
+// Launches nsteps steps kernel by kernel: passes of the most fused steps the
+// handle allows while that many remain, then shorter ones (with capture: the
+// moments of steps i .. i + ns - 1 of a pass, one capture block apart).
+static int launch_steps(tflbm_sim *sim, int64_t nsteps, void *d_capture, hipStream_t st) {
+  if (sim->block.ns > 0) return launch_block_steps(sim, nsteps, d_capture, st);
+  const size_t cap_bytes = tflbm_capture_bytes(sim);
+  const int ns_max = march_steps_per_pass(sim);
   int64_t i = 0;
   while (i < nsteps) {
     const int ns = (int)(nsteps - i < ns_max ? nsteps - i : ns_max);
@@ -469,7 +501,7 @@ int64_t tflbm_step_count(const tflbm_sim *sim) { return sim ? sim->steps : -1; }
 int tflbm_steps_per_pass(const tflbm_sim *sim) {
   if (!sim) return TFLBM_EINVAL;
   if (!sim->initialised) return TFLBM_ESTATE;
-  return steps_per_pass(sim);
+  return sim->block.ns > 0 ? sim->block.ns : march_steps_per_pass(sim);
 }
 
 int tflbm_step_graphs(const tflbm_sim *sim) {

@@ -40,6 +40,31 @@ hipError_t launch_mass(int prec, const StepArgs &A, double *partial, int np, dou
 // aligned) by the library's record-copy kernel.
 hipError_t launch_copy(const void *src, void *dst, size_t bytes, hipStream_t s);
 
+// What a block kernel needs beyond StepArgs (whose launch shape it ignores).
+struct BlockArgs {
+  StepArgs s;
+  int ns;             // time steps of this pass
+  int halo;           // columns and rows the tile loses per side
+  int bw, bh;         // output columns and rows of a tile
+  int ntx;            // tiles per row of tiles
+  unsigned inv_ntx;   // 2^32 / ntx rounded down, at most 2^32 - 1
+  int ntiles, per_xcd;
+  int kf;             // FieldKind
+  int in_mom, out_mom;  // omega = 1: the pass reads / writes moments instead of populations
+  float ksign;        // the sign of phi(h) = (h_*/h)^9 - (h_*/h)^3: -1 for the exponents (3, 9)
+};
+
+struct BlockShape {
+  int r, nw;   // rows per wavefront, wavefronts per workgroup
+  bool pairs;  // the shape takes a surface tension field
+};
+// A block plan: index of the shape and most steps per pass (0: no plan).
+struct BlockPlan {
+  int shape = 0, ns = 0;
+};
+// ns steps of every tile in one launch (block.h).
+hipError_t launch_block(int prec, bool w1, int shape, const BlockArgs &A, hipStream_t s);
+
 // Reverse-mode kernels.
 struct AdjArgs;
 // w1: omega = 1, the adjoint carried between steps as three fields per site.

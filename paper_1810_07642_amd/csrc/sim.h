@@ -5,6 +5,7 @@
 
 #include "../../include/tflbm.h"
 #include "device.h"
+#include "launch.h"
 
 struct tflbm_sim {
   tflbm_params p;
@@ -31,6 +32,8 @@ struct tflbm_sim {
   bool fuse3_fits = false;  // three steps per pass (omega = 1) beat two on this lattice
   bool rem2_general = false;  // FP64, omega = 1, three steps per pass: two-step passes run the general stages
   bool w1 = false;        // omega = 1 (tau = 1): the stages without a population history
+  // lattices too small to fill the GPU with marching strips: the block kernel
+  tflbm::BlockPlan block;
   // launch-bound lattices: blocks of steps replayed from captured graphs, one
   // per starting buffer parity, captured on a stream of the library's own
   bool graphs = false;
@@ -65,6 +68,11 @@ int choose_rows(int ny, int nstrips, int slots, int min_rows, const char *env_na
 
 // Chooses the launch shapes of the step kernels (needs the device).
 void plan_launches(tflbm_sim *s);
+
+// The block kernel's plan for the handle (false: the marching kernel is to run)
+// and its launch shape for a pass of ns steps.
+bool plan_block(const tflbm_sim *s, BlockPlan &best);
+void shape_block(const tflbm_sim *s, int shape, int ns, BlockArgs &A);
 
 // Releases the captured step graphs of `s`, after waiting for the device.
 void drop_graphs(tflbm_sim *s);

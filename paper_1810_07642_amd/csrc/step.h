@@ -230,7 +230,7 @@ __device__ __forceinline__ void kappa_cols(const KapBuf<P, KF> &k, typename Form
 template <typename T> struct Coef {
   T omega, om1, nu, hstar, href, g, ax, ay, kap0, cA, cD, three_delta2, six_delta, mgam, mgam6;
   int n_exp, m_exp;
-  __device__ explicit Coef(const StepArgs &A) {
+  __host__ __device__ explicit Coef(const StepArgs &A) {
     omega = (T)A.omega;
     om1 = (T)(1.0 - A.omega);
     nu = (T)A.nu;
@@ -268,6 +268,91 @@ __device__ __forceinline__ void shift_x(int l, const T *in, T *out) {
     for (int v = 0; v < V - 1; ++v) out[v] = in[v + 1];
     out[V - 1] = from_right(in[0]);
   }
+}
+
+// j = sum_l c_l d_l through the differences of opposite populations.
+template <typename T> __device__ __forceinline__ void momentum(const T (&f)[9], T &jx, T &jy) {
+  const T d15 = f[1] - f[5], d37 = f[3] - f[7];
+  const T d26 = f[2] - f[6], d84 = f[8] - f[4];
+  jx = (d15 + d26) + d84;
+  jy = (d37 + d26) - d84;
+}
+
+// 6 lap h = 6 lap dh = 4 sum_axes + sum_diagonals - 20 dh of one site (eq.
+// "n_laplace") from dh at the columns x - 1, x, x + 1 of the rows y + 1 (hn),
+// y (hc) and y - 1 (hp).
+template <typename T> __device__ __forceinline__ T laplacian6(const T *hn, const T *hc, const T *hp) {
+  T odd = hc[2];
+  odd += hn[1];
+  odd += hc[0];
+  odd += hp[1];
+  T even = hn[2];
+  even += hn[0];
+  even += hp[0];
+  even += hp[2];
+  return madd(T(-20), hc[1], madd(T(4), odd, even));
+}
+
+// Post-collision deviations of one site (eqs. "LBE", "equilibria", "force",
+// "forcefric", "alphafric") from its h, 1/h, dh = h - href and j, the pressure
+// gradient (gx, gy) and, unless omega = 1 (W1), its pre-collision deviations f.
+// W1 leaves the factor omega out and G0 (g = 0) the hydrostatic part: the
+// products by one and the sums with zero that the general form spends on them.
+template <typename T, bool W1, bool G0>
+__device__ __forceinline__ void collide(const Coef<T> &C, T h, T inv_h, T gx, T gy, T dh, T jx, T jy, const T (&f)[9],
+                                        T (&post)[9]) {
+  const T ux = jx * inv_h, uy = jy * inv_h;
+
+  // F = h (a - grad p) - nu alpha(h) u, alpha = 6 h / (2 h^2 + 6 delta h + 3 delta^2)
+  const T alpha = T(6) * h * recip(madd(T(2) * h, h, madd(C.six_delta, h, C.three_delta2)));
+  const T fric = C.nu * alpha;
+  const T Fx = madd(h, C.ax - gx, -fric * ux);
+  const T Fy = madd(h, C.ay - gy, -fric * uy);
+
+  // equilibrium (lattice speed 1 in the printed denominators) minus the
+  // stored shift E_l(href, 0), with q = g (h^2 - href^2) = g dh (h + href):
+  //   rest: dh - 5 q/6 - 2 h u^2/3
+  //   axes: q/6 + h ((c.u)/3 + (c.u)^2/2 - u^2/6)
+  //   diagonals: q/24 + h ((c.u)/12 + (c.u)^2/8 - u^2/24)
+  // BGK with forcing: d + omega (deq - d) + 3 w_l c_l.F.  Opposite
+  // populations l, -l share the even part in c and differ in the sign of
+  // the odd part: post = (1 - omega) d + E +- O with
+  //   E = omega h ((c.u)^2 w2 - u^2 w0) + omega q w0,
+  //   O = w1 (omega h c.u + c.F),  (w0, w1, w2) = (1/6, 1/3, 1/2) on the
+  //   axes and (1/24, 1/12, 1/8) on the diagonals.
+  const T usq = madd(ux, ux, uy * uy);
+  const T hom = W1 ? h : h * C.omega;
+  const T odh = W1 ? dh : C.omega * dh;
+  T e0, evA, evD;  // E of the rest population, and without (c.u)^2 on the axes and diagonals
+  if constexpr (G0) {
+    e0 = madd(hom, usq * T(-2.0 / 3.0), odh);
+    evA = hom * (usq * T(-1.0 / 6.0));
+    evD = hom * (usq * T(-1.0 / 24.0));
+  } else {
+    const T q = C.g * dh * (h + C.href);
+    const T G = W1 ? q : C.omega * q;
+    e0 = madd(hom, usq * T(-2.0 / 3.0), madd(G, T(-5.0 / 6.0), odh));
+    evA = madd(hom, usq * T(-1.0 / 6.0), G * T(1.0 / 6.0));
+    evD = madd(hom, usq * T(-1.0 / 24.0), G * T(1.0 / 24.0));
+  }
+  if constexpr (W1) post[0] = e0;
+  else post[0] = madd(C.om1, f[0], e0);
+  auto opposite = [&](int lp, int lm, T cu, T cF, T ev, T w1, T w2) {
+    const T hc = hom * cu;
+    const T E = madd(hc, cu * w2, ev);
+    const T O = hc + cF;
+    if constexpr (W1) {
+      post[lp] = madd(O, w1, E);
+      post[lm] = madd(-O, w1, E);
+    } else {
+      post[lp] = madd(O, w1, madd(C.om1, f[lp], E));
+      post[lm] = madd(-O, w1, madd(C.om1, f[lm], E));
+    }
+  };
+  opposite(1, 5, ux, Fx, evA, T(1.0 / 3.0), T(0.5));
+  opposite(3, 7, uy, Fy, evA, T(1.0 / 3.0), T(0.5));
+  opposite(2, 6, ux + uy, Fx + Fy, evD, T(1.0 / 12.0), T(0.125));
+  opposite(4, 8, uy - ux, Fy - Fx, evD, T(1.0 / 12.0), T(0.125));
 }
 
 // One time step applied row by row to a marching strip.  ingest(k, ...)
@@ -335,10 +420,12 @@ template <int P, int KF, bool W1 = false> struct Stage {
       }
 #pragma unroll
       for (int v = 0; v < V; ++v) {
-        const T d15 = f[1][v] - f[5][v], d37 = f[3][v] - f[7][v];
-        const T d26 = f[2][v] - f[6][v], d84 = f[8][v] - f[4][v];
-        jhist[slot][0][V * lane + v] = (d15 + d26) + d84;
-        jhist[slot][1][V * lane + v] = (d37 + d26) - d84;
+        T fv[9], jx, jy;
+#pragma unroll
+        for (int l = 0; l < 9; ++l) fv[l] = f[l][v];
+        momentum(fv, jx, jy);
+        jhist[slot][0][V * lane + v] = jx;
+        jhist[slot][1][V * lane + v] = jy;
       }
     } else {
       // row r-2 leaves the LDS slot that row r takes over
@@ -363,17 +450,8 @@ template <int P, int KF, bool W1 = false> struct Stage {
       T pc[V + 2];
 #pragma unroll
       for (int v = 0; v < V; ++v) {
-        T odd = h1[v + 2];
-        odd += h0[v + 1];
-        odd += h1[v];
-        odd += h2[v + 1];
-        T even = h0[v + 2];
-        even += h0[v];
-        even += h2[v];
-        even += h2[v + 2];
         const T hc = C.href + h1[v + 1];
-        // 6 lap h = 6 lap dh = 4 sum_axes + sum_diagonals - 20 dh
-        const T lap6 = madd(T(-20), h1[v + 1], madd(T(4), odd, even));
+        const T lap6 = laplacian6(&h0[v], &h1[v], &h2[v]);
         const T phi = disjoining(C.hstar * recip(hc), C.n_exp, C.m_exp);
         if constexpr (KF == kGammaKappa) {
           // per-site (-gamma/6, -gamma kappa), rounded at init as the scalar
@@ -401,62 +479,19 @@ template <int P, int KF, bool W1 = false> struct Stage {
         const T gy = sm1[v] - sm3[v];
 
         const T dh = h2[1 + v];
-        const T h = C.href + dh;
-        T jx, jy;
+        T jx, jy, fv[9], pv[9];
         if constexpr (W1) {
           jx = jx2[v];
           jy = jy2[v];
         } else {
-          // j = sum_l c_l d_l through the differences of opposite populations
-          const T d15 = f2[1][v] - f2[5][v], d37 = f2[3][v] - f2[7][v];
-          const T d26 = f2[2][v] - f2[6][v], d84 = f2[8][v] - f2[4][v];
-          jx = (d15 + d26) + d84;
-          jy = (d37 + d26) - d84;
+#pragma unroll
+          for (int l = 0; l < 9; ++l) fv[l] = f2[l][v];
+          momentum(fv, jx, jy);
         }
-        const T inv_h = recip(h);
-        const T ux = jx * inv_h, uy = jy * inv_h;
-
-        // F = h (a - grad p) - nu alpha(h) u, alpha = 6 h / (2 h^2 + 6 delta h + 3 delta^2)
-        const T alpha = T(6) * h * recip(madd(T(2) * h, h, madd(C.six_delta, h, C.three_delta2)));
-        const T fric = C.nu * alpha;
-        const T Fx = madd(h, C.ax - gx, -fric * ux);
-        const T Fy = madd(h, C.ay - gy, -fric * uy);
-
-        // equilibrium (lattice speed 1 in the printed denominators) minus the
-        // stored shift E_l(href, 0), with q = g (h^2 - href^2) = g dh (h + href):
-        //   rest: dh - 5 q/6 - 2 h u^2/3
-        //   axes: q/6 + h ((c.u)/3 + (c.u)^2/2 - u^2/6)
-        //   diagonals: q/24 + h ((c.u)/12 + (c.u)^2/8 - u^2/24)
-        // BGK with forcing: d + omega (deq - d) + 3 w_l c_l.F.  Opposite
-        // populations l, -l share the even part in c and differ in the sign of
-        // the odd part: post = (1 - omega) d + E +- O with
-        //   E = omega h ((c.u)^2 w2 - u^2 w0) + omega q w0,
-        //   O = w1 (omega h c.u + c.F),  (w0, w1, w2) = (1/6, 1/3, 1/2) on the
-        //   axes and (1/24, 1/12, 1/8) on the diagonals.
-        const T usq = madd(ux, ux, uy * uy);
-        const T hom = h * C.omega;
-        const T G = C.omega * (C.g * dh * (h + C.href));  // omega q
-        const T e0 = madd(hom, usq * T(-2.0 / 3.0), madd(G, T(-5.0 / 6.0), C.omega * dh));
-        if constexpr (W1) post[0][v] = e0;
-        else post[0][v] = madd(C.om1, f2[0][v], e0);
-        const T evA = madd(hom, usq * T(-1.0 / 6.0), G * T(1.0 / 6.0));    // E without (c.u)^2, axes
-        const T evD = madd(hom, usq * T(-1.0 / 24.0), G * T(1.0 / 24.0));  // and diagonals
-        auto opposite = [&](int lp, int lm, T cu, T cF, T ev, T w1, T w2) {
-          const T hc = hom * cu;
-          const T E = madd(hc, cu * w2, ev);
-          const T O = hc + cF;
-          if constexpr (W1) {
-            post[lp][v] = madd(O, w1, E);
-            post[lm][v] = madd(-O, w1, E);
-          } else {
-            post[lp][v] = madd(O, w1, madd(C.om1, f2[lp][v], E));
-            post[lm][v] = madd(-O, w1, madd(C.om1, f2[lm][v], E));
-          }
-        };
-        opposite(1, 5, ux, Fx, evA, T(1.0 / 3.0), T(0.5));
-        opposite(3, 7, uy, Fy, evA, T(1.0 / 3.0), T(0.5));
-        opposite(2, 6, ux + uy, Fx + Fy, evD, T(1.0 / 12.0), T(0.125));
-        opposite(4, 8, uy - ux, Fy - Fx, evD, T(1.0 / 12.0), T(0.125));
+        const T h = C.href + dh;
+        collide<T, W1, false>(C, h, recip(h), gx, gy, dh, jx, jy, fv, pv);
+#pragma unroll
+        for (int l = 0; l < 9; ++l) post[l][v] = pv[l];
         hv[v] = dh;
         jxv[v] = jx;
         jyv[v] = jy;

@@ -1,0 +1,82 @@
+"""The block kernel (several steps of a tile per launch, its state in
+registers) against the marching kernel at one step per pass: the same bits in
+the state (padding included), the readout and the captures, for every shape at
+its smallest, a middle and its largest number of steps per pass."""
+import os
+
+import pytest
+import torch
+
+from gpu_common import banner, random_case
+from test_gpu_gamma import gamma_field
+
+pytestmark = pytest.mark.gpu
+
+# lattices smaller than a tile in one or both directions (periodic images
+# inside a tile), ragged ones, and whole multiples of no tile
+LATTICES = [(1, 1), (5, 3), (23, 37), (130, 97), (6, 300), (300, 6), (70, 150)]
+# rows of a tile per shape (rows per wavefront x wavefronts)
+SHAPES = {("fp32", 1.0): (32, 48, 80), ("fp32", 0.9): (32, 24), ("fp64", 1.0): (32, 36, 48), ("fp64", 0.9): (16, 24)}
+CASES = [(prec, tau, shape) for (prec, tau), rows in SHAPES.items() for shape in range(len(rows))]
+
+
+def run(prec, ny, nx, field, steps, env, p):
+    from paper_1810_07642_amd import Sim
+    os.environ.update(env)
+    try:
+        sim = Sim(nx, ny, prec, gamma_field=field == "gamma", **p)
+        h0, th = random_case(ny, nx, 61)
+        sim.init(h0, None if field == "uniform" else th, gamma_field(ny, nx, 62) if field == "gamma" else None)
+    finally:
+        for k in env:
+            del os.environ[k]
+    sim.step(steps)
+    cap = torch.zeros(5 * sim.capture_bytes(), dtype=torch.uint8, device=sim.device)
+    mid = tuple(t.cpu() for t in sim.read())
+    sim.step_capture(5, cap)
+    sim.check()
+    return (sim.state_save().cpu(), cap.cpu()) + mid + tuple(t.cpu() for t in sim.read()), sim.steps_per_pass
+
+
+@pytest.mark.parametrize("g", [1e-3, 0.0])
+@pytest.mark.parametrize("prec,tau,shape", CASES)
+def test_block_kernel_equals_marching_kernel_bitwise(prec, tau, shape, g):
+    rows = SHAPES[(prec, tau)][shape]
+    most = min((rows - 2) // 6, 9)  # two output rows, eight output columns of 64
+    # the shape of four FP64 rows per wavefront takes no surface tension field
+    fields = ("theta", "uniform") if (prec, tau, shape) == ("fp64", 1.0, 2) else ("theta", "uniform", "gamma")
+    for (ny, nx) in LATTICES:
+        for n, m in ((9, 3), (3, 9)):
+            p = dict(tau=tau, gamma=0.01, g=g, hstar=0.1, delta=1.0, ax=1e-5, ay=-1e-5, n=n, m=m, href=0.4)
+            for field in fields if n == 9 else ("theta",):
+                banner(f"block kernel: {prec} tau={tau} shape {shape} g={g} {ny}x{nx} {field} n={n}")
+                ref, _ = run(prec, ny, nx, field, 11, {"TFLBM_FUSE": "1"}, p)
+                for ns in sorted({1, 2, most}):
+                    got, spp = run(prec, ny, nx, field, 11,
+                                   {"TFLBM_BLOCK": str(ns), "TFLBM_BLOCK_SHAPE": str(shape)}, p)
+                    assert spp == ns
+                    for a, b in zip(got, ref):
+                        assert torch.equal(a, b), (ny, nx, field, ns)
+
+
+def test_block_kernel_flags_bad_heights():
+    """h <= 0 and NaN at one site are reported whichever tile holds it."""
+    from paper_1810_07642_amd import Sim
+    from paper_1810_07642_amd._lib import TFLBM_ENONFINITE, TFLBM_OK
+    os.environ["TFLBM_BLOCK"] = "3"
+    try:
+        for bad in (-0.1, float("nan")):
+            for at in ((0, 0), (40, 99), (69, 149)):
+                sim = Sim(150, 70, "fp32", hstar=0.1)
+                h0 = torch.full((70, 150), 0.3, dtype=torch.float64)
+                sim.init(h0)
+                sim.step(3)
+                assert sim.status() == TFLBM_OK
+                # a bad site that enters through a checkpoint, not through init's own check
+                h0[at] = bad
+                other = Sim(150, 70, "fp32", hstar=0.1).init(h0)
+                sim.state_load(other.state_save(), 0)
+                sim.step(3)
+                assert sim.status() == TFLBM_ENONFINITE, (bad, at)
+    finally:
+        del os.environ["TFLBM_BLOCK"]
