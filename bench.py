@@ -7,8 +7,9 @@ pi/9 and pi/4 (sine-smoothed edges, width 8), flat film h0 = 0.1 + 1e-4
 U(-1, 1) (seed 2), h_* = 0.09, gamma = 0.01, tau = 1, delta = 1.  The headline
 value is the FP64 step, the arithmetic of the paper's own benchmark table
 (Sec. IV).  A "step" is one lattice time step of the whole grid; the library
-runs two steps per launch of its fused step kernel (the intermediate state
-stays on chip); MLUPS = nx ny steps / (t 1e6) (Sec. IV).
+runs up to three steps per launch of its fused step kernels (the intermediate
+state stays on chip), and with tau = 1 in FP64 and FP32 the launches of a call
+hand each other the moments h and j alone; MLUPS = nx ny steps / (t 1e6) (Sec. IV).
 
     python bench.py [--gpus 1] [--steps K] [--warmup W]
 
@@ -33,9 +34,14 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, AMD published
-# Algorithmic bytes per site of one pass of the fused step kernel: read and
-# write each of the 9 populations once, plus the kappa field read once.
-BYTES_PER_SITE = {"fp64": 152, "fp32": 76, "fp16s": 44}
+# Algorithmic bytes per site of one pass of the fused step kernel at tau = 1:
+# FP64 and FP32 read and write the three moments once, plus the kappa field read
+# once; the first pass of a call reads, and the last one writes, the nine
+# populations instead (CALL_BYTES more per site and call).  FP16S and the
+# general stages read and write the populations in every pass.
+BYTES_PER_SITE = {"fp64": 56, "fp32": 28, "fp16s": 44}
+CALL_BYTES = {"fp64": 96, "fp32": 48, "fp16s": 0}
+GENERAL_BYTES = {"fp64": 152, "fp32": 76, "fp16s": 44}
 HREF = {"fp64": 0.0, "fp32": 0.1, "fp16s": 0.1}  # storage reference height: the film's mean
 # Reverse pass, two steps per launch, FP32 adjoint with FP64 kappa gradient,
 # at tau = 1 (the adjoint between steps as three fields per site): fields
@@ -124,7 +130,7 @@ def general_stages(sims, p, h0, th, ceil_gbs):
         sim.check()
         spp = sim.steps_per_pass
         out[prec] = {"mlups": round(sites * EXTRA_STEPS / (ms * 1e-3) / 1e6, 1), "steps_per_pass": spp,
-                     "roofline_frac": roofline_block("general stages", BYTES_PER_SITE[prec] * sites,
+                     "roofline_frac": roofline_block("general stages", GENERAL_BYTES[prec] * sites,
                                                      ms / launches(EXTRA_STEPS, spp), None, ceil_gbs)["frac"]}
         del sim
         torch.cuda.empty_cache()
@@ -147,9 +153,14 @@ def launches(steps, per_pass):
     return -(-steps // per_pass)
 
 
+def launch_bytes(prec, steps, per_pass, sites):
+    """Algorithmic bytes of a launch, averaged over a call of `steps` steps."""
+    return (BYTES_PER_SITE[prec] + CALL_BYTES[prec] / launches(steps, per_pass)) * sites
+
+
 def step_kernel_name(sim, prec):
-    spp = sim.steps_per_pass
-    return f"step_kernel<{prec}, kappa field, {spp} fused steps{', omega = 1 stages' if sim.params.tau == 1.0 else ''}>"
+    name = "step_kernel" if prec == "fp16s" else "march_kernel"
+    return f"{name}<{prec}, kappa field, {sim.steps_per_pass} fused steps, omega = 1>"
 
 
 def roofline_block(kernel, bytes_per_launch, launch_ms, traffic, ceiling_gbs, steps_per_launch=2):
@@ -493,7 +504,7 @@ def main():
     mlups = sites * args.steps / (ms64 * 1e-3) / 1e6
     spp64 = sims["fp64"].steps_per_pass
     launch_ms = ms64 / launches(args.steps, spp64)
-    roof = roofline_block(step_kernel_name(sims["fp64"], "fp64"), BYTES_PER_SITE["fp64"] * sites,
+    roof = roofline_block(step_kernel_name(sims["fp64"], "fp64"), launch_bytes("fp64", args.steps, spp64, sites),
                           launch_ms, committed_traffic("fp64"), ceil_gbs, steps_per_launch=spp64)
     roof["per_step_equivalent_GBps"] = round(BYTES_PER_SITE["fp64"] * sites / (ms_step * 1e-3) / 1e9, 1)
     line = {
@@ -530,7 +541,8 @@ def main():
             forms[prec] = {"mlups": round(ml, 1), "ms_per_step": round(ms / EXTRA_STEPS, 5),
                            "steps_timed": EXTRA_STEPS, "href": HREF[prec], "steps_per_pass": spp,
                            "roofline": roofline_block(step_kernel_name(sims[prec], prec),
-                                                      BYTES_PER_SITE[prec] * sites, lm, committed_traffic(prec),
+                                                      launch_bytes(prec, EXTRA_STEPS, spp, sites), lm,
+                                                      committed_traffic(prec),
                                                       ceil_gbs, steps_per_launch=spp)}
             forms[prec]["roofline"]["per_step_equivalent_GBps"] = round(
                 BYTES_PER_SITE[prec] * sites / (ms / EXTRA_STEPS * 1e-3) / 1e9, 1)

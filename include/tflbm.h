@@ -142,6 +142,10 @@ int tflbm_check_params(const tflbm_params *p);
  * with at most n steps per pass; by default on lattices where it is faster
  * than the marching kernels, unless one of the variables above asks for a
  * shape of theirs) and TFLBM_BLOCK_SHAPE (its tile shape),
+ * TFLBM_MARCH=0, 2 or 3 (read at tflbm_init: with tau = 1, whether the marching
+ * kernels' passes of a call hand over moments instead of populations, and two or
+ * three steps per such pass; by default by lattice size; the same bits) and
+ * TFLBM_MARCH_ROWS (rows per chunk of those passes),
  * TFLBM_GRAPH=0 or 1 (read at tflbm_init: whether tflbm_step replays blocks
  * of steps from graphs; by default on lattices of at most 2^20 sites). */
 int tflbm_create(const tflbm_params *p, tflbm_sim **out);

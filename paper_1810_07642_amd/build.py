@@ -18,7 +18,10 @@ UNITS = [(f"step_{form}_{'w1' if w1 else 'general'}", "step_form.hip", [f"-DSTEP
          for form, P in (("f16s", "kF16S"), ("f32", "kF32"), ("f64", "kF64")) for w1 in (1, 0)]
 UNITS += [(f"block_{form}_{'w1' if w1 else 'general'}", "block_form.hip", [f"-DSTEP_FORM={P}", f"-DSTEP_W1={w1}"])
           for form, P in (("f32", "kF32"), ("f64", "kF64")) for w1 in (1, 0)]
-UNITS += [(s[:-4], s, []) for s in ("adj.hip", "fwd.hip", "block.hip", "api.hip", "diag.hip", "noalloc.hip")]
+UNITS = [(f"march_{form}_{field}", "march_form.hip", [f"-DSTEP_FORM={P}", f"-DMARCH_FIELD={F}"])
+         for form, P in (("f32", "kF32"), ("f64", "kF64"))
+         for field, F in (("kappa", "kKappa"), ("uniform", "kNoField"))] + UNITS
+UNITS += [(s[:-4], s, []) for s in ("adj.hip", "fwd.hip", "block.hip", "march.hip", "api.hip", "diag.hip", "noalloc.hip")]
 SOURCES = sorted({src for _, src, _ in UNITS})
 OBJ = os.path.join(PKG, "_build")
 ARCH = "gfx950"

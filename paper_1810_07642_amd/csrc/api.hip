@@ -159,6 +159,7 @@ void plan_launches(tflbm_sim *s) {
   // pass (4096^2: 188.8 vs 284.8 us).
   s->adj_fuse_fits = !(s->w1 && s->p.prec == kF64) &&
                      (int64_t)s->adj_nstrips * ((ny + kMinRowsAdj2 - 1) / kMinRowsAdj2) > (int64_t)aocc2 * cus;
+  plan_march(s, cus);
   // the block kernel, unless a variable asks for a shape of the marching one
   bool march = s->fuse != 0;
   for (const char *v : {"TFLBM_ROWS", "TFLBM_ROWS2", "TFLBM_ROWS3"}) march = march || std::getenv(v) != nullptr;
@@ -405,6 +406,31 @@ static int launch_block_steps(tflbm_sim *sim, int64_t nsteps, void *d_capture, h
   return TFLBM_OK;
 }
 
+// The same by passes that hand over moments.
+static int launch_march_steps(tflbm_sim *sim, const MarchSplit &sp, void *d_capture, hipStream_t st) {
+  const size_t cap_bytes = tflbm_capture_bytes(sim);
+  int64_t done = 0;
+  for (int64_t i = 0; i < sp.passes; ++i) {
+    const bool last = i + 1 == sp.passes;
+    // the first pass has two steps, the last one three if any has
+    const int ns = i == 0 ? 2 : (last ? (sp.threes > 0 ? 3 : 2) : (i < sp.threes ? 3 : 2));
+    const int kind = i == 0 ? kPopMom2 : (last ? (ns == 3 ? kMomPop3 : kMomPop2) : (ns == 3 ? kMom3 : kMom2));
+    const MarchShape &m = sim->march_shape[kind];
+    StepArgs A = make_step_args(sim);
+    A.capture = d_capture ? (char *)d_capture + (size_t)done * cap_bytes : nullptr;
+    A.H = m.rows;
+    A.nstrips = m.nstrips;
+    A.ntiles = m.ntiles;
+    A.per_xcd = m.per_xcd;
+    const int rc = hip_status(sim, launch_march(sim->p.prec, kind, A, sim->kfield, d_capture != nullptr, nullptr, st));
+    if (rc) return rc;
+    sim->cur ^= 1;
+    sim->steps += ns;
+    done += ns;
+  }
+  return TFLBM_OK;
+}
+
 // Launches nsteps steps kernel by kernel: passes of the most fused steps the
 // handle allows while that many remain, then shorter ones (with capture: the
 // moments of steps i .. i + ns - 1 of a pass, one capture block apart).
@@ -412,6 +438,9 @@ static int launch_steps(tflbm_sim *sim, int64_t nsteps, void *d_capture, hipStre
   if (sim->block.ns > 0) return launch_block_steps(sim, nsteps, d_capture, st);
   const size_t cap_bytes = tflbm_capture_bytes(sim);
   const int ns_max = march_steps_per_pass(sim);
+  MarchSplit sp;
+  if (sim->march_ns > 0 && split_march(nsteps, (nsteps + ns_max - 1) / ns_max, sim->march_ns, sp))
+    return launch_march_steps(sim, sp, d_capture, st);
   int64_t i = 0;
   while (i < nsteps) {
     const int ns = (int)(nsteps - i < ns_max ? nsteps - i : ns_max);
@@ -501,7 +530,7 @@ int64_t tflbm_step_count(const tflbm_sim *sim) { return sim ? sim->steps : -1; }
 int tflbm_steps_per_pass(const tflbm_sim *sim) {
   if (!sim) return TFLBM_EINVAL;
   if (!sim->initialised) return TFLBM_ESTATE;
-  return sim->block.ns > 0 ? sim->block.ns : march_steps_per_pass(sim);
+  return sim->block.ns > 0 ? sim->block.ns : (sim->march_ns > 0 ? 3 : march_steps_per_pass(sim));
 }
 
 int tflbm_step_graphs(const tflbm_sim *sim) {

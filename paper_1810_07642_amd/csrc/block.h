@@ -210,10 +210,7 @@ __global__ __launch_bounds__(64 * NW) void block_kernel(BlockArgs A, Coef<typena
 #pragma unroll
       for (int i = 0; i < R; ++i) hx[1 + i][1] = dh[i];
 #pragma unroll
-      for (int i = 0; i < R + 2; ++i) {
-        hx[i][0] = from_left(hx[i][1]);
-        hx[i][2] = from_right(hx[i][1]);
-      }
+      for (int i = 0; i < R + 2; ++i) row_sums<1>(hx[i]);
 #pragma unroll
       for (int i = 0; i < R; ++i) {
         ih[i] = recip(C.href + dh[i]);

@@ -21,16 +21,19 @@ extern template hipError_t launch_block_form<kF32, true>(int, const BlockArgs &,
 //   launch + step ns + load (row_load rows + row_step active row steps),
 // with the rows of one workgroup and `load` the workgroups per CU, rounded up
 // to whole ones as far as `whole` says (a CU is busy until its last one ends).
-// march0..2: time of one step of the marching kernel over n strip rows,
-// march0 + march1 min(n, 2500) + march2 max(n - 2500, 0).
+// march0..2: time of one step of the marching kernels over n strip rows,
+// march0 + march1 min(n, 2500) + march2 max(n - 2500, 0); moments: march2 where
+// their passes hand over moments (march.h).
 struct BlockModel {
-  double launch, step, row_load, row_step, whole, march0, march1, march2;
+  double launch, step, row_load, row_step, whole, march0, march1, march2, moments;
   int shapes;  // shapes of the form (block_shape)
 };
 static const BlockModel &block_model(int prec, bool w1) {
   static const BlockModel t[2][2] = {
-      {{1.35, 0.00, 0.263, 0.0445, 1.0, 4.0, 1.9e-3, 0.72e-3, 2}, {1.14, 0.44, 0.107, 0.0682, 1.0, 3.8, 1.8e-3, 0.50e-3, 3}},
-      {{2.99, 0.21, 0.050, 0.0693, 0.74, 5.0, 1.6e-3, 0.95e-3, 2}, {2.98, 0.25, 0.034, 0.0562, 0.58, 4.6, 1.8e-3, 0.75e-3, 3}}};
+      {{1.35, 0.00, 0.263, 0.0445, 1.0, 4.0, 1.9e-3, 0.72e-3, 0, 2},
+       {1.14, 0.44, 0.107, 0.0682, 1.0, 3.8, 1.8e-3, 0.50e-3, 0.28e-3, 3}},
+      {{2.99, 0.21, 0.050, 0.0693, 0.74, 5.0, 1.6e-3, 0.95e-3, 0, 2},
+       {2.98, 0.25, 0.034, 0.0562, 0.58, 4.6, 1.8e-3, 0.75e-3, 0.385e-3, 3}}};
   return t[prec == kF64 ? 0 : 1][w1 ? 1 : 0];
 }
 
@@ -82,7 +85,8 @@ bool plan_block(const tflbm_sim *s, BlockPlan &best) {
   }
   if (best.ns == 0) return false;
   const double n = (double)s->nstrips * p.ny;
-  const double march = m.march0 + m.march1 * (n < 2500 ? n : 2500) + m.march2 * (n < 2500 ? 0 : n - 2500);
+  const double march = m.march0 + m.march1 * (n < 2500 ? n : 2500) +
+                       (s->march_ns > 0 ? m.moments : m.march2) * (n < 2500 ? 0 : n - 2500);
   return forced || best_t < 0.9 * march;  // (a tie stays with the marching kernel: FP64 1024^2)
 }
 

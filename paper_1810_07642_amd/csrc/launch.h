@@ -65,6 +65,15 @@ struct BlockPlan {
 // ns steps of every tile in one launch (block.h).
 hipError_t launch_block(int prec, bool w1, int shape, const BlockArgs &A, hipStream_t s);
 
+// Passes that hand over moments (march.h): two or three steps, populations or
+// moments in and out.
+enum MarchKind { kPopMom2 = 0, kMom2 = 1, kMom3 = 2, kMomPop2 = 3, kMomPop3 = 4, kMarchKinds = 5 };
+struct MarchShape {
+  int rows, nstrips, ntiles, per_xcd;
+};
+// occ: only the resident workgroups per CU of the pass's kernel, without launching.
+hipError_t launch_march(int prec, int kind, const StepArgs &A, int kf, bool cap, int *occ, hipStream_t s);
+
 // Reverse-mode kernels.
 struct AdjArgs;
 // w1: omega = 1, the adjoint carried between steps as three fields per site.

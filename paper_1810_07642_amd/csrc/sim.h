@@ -32,6 +32,9 @@ struct tflbm_sim {
   bool fuse3_fits = false;  // three steps per pass (omega = 1) beat two on this lattice
   bool rem2_general = false;  // FP64, omega = 1, three steps per pass: two-step passes run the general stages
   bool w1 = false;        // omega = 1 (tau = 1): the stages without a population history
+  // passes that hand over moments: steps per pass (0: none) and launch shapes
+  int march_ns = 0;
+  tflbm::MarchShape march_shape[tflbm::kMarchKinds] = {};
   // lattices too small to fill the GPU with marching strips: the block kernel
   tflbm::BlockPlan block;
   // launch-bound lattices: blocks of steps replayed from captured graphs, one
@@ -73,6 +76,16 @@ void plan_launches(tflbm_sim *s);
 // and its launch shape for a pass of ns steps.
 bool plan_block(const tflbm_sim *s, BlockPlan &best);
 void shape_block(const tflbm_sim *s, int shape, int ns, BlockArgs &A);
+
+// Passes that hand over moments: their plan, and the split of a call of nsteps
+// steps into `passes` passes, the first of two steps, `threes` of the others of
+// three and the rest of two.  False where there is none with a number of passes
+// that is even or odd with passes_before.
+struct MarchSplit {
+  int64_t passes, threes;
+};
+void plan_march(tflbm_sim *s, int cus);
+bool split_march(int64_t nsteps, int64_t passes_before, int ns, MarchSplit &sp);
 
 // Releases the captured step graphs of `s`, after waiting for the device.
 void drop_graphs(tflbm_sim *s);

@@ -96,6 +96,31 @@ template <int P> struct Lane {
   bool allvecp;       // wave-uniform: vecp on every lane
   bool pair;          // all V columns are outputs and vec holds
   bool fast_store;    // wave-uniform: every lane has all or none of its columns as outputs, with vec
+
+  // a: the lane's first (unwrapped) column; the strip's outputs are x0 .. xend - 1
+  __device__ __forceinline__ Lane(int a, int x0, int xend, int nx) {
+    constexpr int B = Form<P>::B, RB = Form<P>::RB, ES = sizeof(typename Form<P>::T);
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      col[v] = wrap(a + v, nx);
+      const int blk = col[v] / B;
+      const int pos = col[v] - blk * B;
+      oe[v] = blk * RB + pos * ES;
+      oc[v] = blk * cap_record_bytes<P>() + pos * ES;
+      o16[v] = blk * RB + pos * 2;
+      out[v] = (a + v >= x0) && (a + v < xend);
+    }
+    vec = true;
+    vecp = true;
+    if constexpr (V == 2) {
+      vec = (col[1] == col[0] + 1) && (col[0] / B == col[1] / B) && ((col[0] & 1) == 0);
+      vecp = (col[1] == col[0] + 1) && ((col[0] & 1) == 0);
+    }
+    pair = out[0] && out[V - 1] && vec;
+    allvec = __all(vec);
+    allvecp = __all(vecp);
+    fast_store = __all(pair || (!out[0] && !out[V - 1]));
+  }
 };
 
 // Loads the stored deviations of all nine populations of one row.  Strips
@@ -279,18 +304,34 @@ template <typename T> __device__ __forceinline__ void momentum(const T (&f)[9], 
 }
 
 // 6 lap h = 6 lap dh = 4 sum_axes + sum_diagonals - 20 dh of one site (eq.
-// "n_laplace") from dh at the columns x - 1, x, x + 1 of the rows y + 1 (hn),
-// y (hc) and y - 1 (hp).
-template <typename T> __device__ __forceinline__ T laplacian6(const T *hn, const T *hc, const T *hp) {
-  T odd = hc[2];
+// "n_laplace") from dh on the rows y + 1 (hn), y (hc) and y - 1 (hp).  FP32
+// takes the columns x - 1, x, x + 1 of each row; FP64 the sum of x - 1 and x + 1
+// and the column x (row_sums): a row's sum serves the three rows around it, so
+// a site takes four additions instead of eight and a row in flight two
+// registers less.
+__device__ __forceinline__ float laplacian6(const float *hn, const float *hc, const float *hp) {
+  float odd = hc[2];
   odd += hn[1];
   odd += hc[0];
   odd += hp[1];
-  T even = hn[2];
+  float even = hn[2];
   even += hn[0];
   even += hp[0];
   even += hp[2];
-  return madd(T(-20), hc[1], madd(T(4), odd, even));
+  return madd(-20.0f, hc[1], madd(4.0f, odd, even));
+}
+__device__ __forceinline__ double laplacian6(const double *hn, const double *hc, const double *hp) {
+  const double odd = hc[0] + (hn[1] + hp[1]), even = hn[0] + hp[0];
+  return madd(-20.0, hc[1], madd(4.0, odd, even));
+}
+// The form of a row that laplacian6 takes, from its columns h[1 .. V].
+template <int V> __device__ __forceinline__ void row_sums(float *h) {
+  h[0] = from_left(h[V]);
+  h[V + 1] = from_right(h[1]);
+}
+template <int V> __device__ __forceinline__ void row_sums(double *h) {
+  static_assert(V == 1, "one FP64 column per lane");
+  h[0] = from_left(h[1]) + from_right(h[1]);
 }
 
 // Post-collision deviations of one site (eqs. "LBE", "equilibria", "force",
@@ -370,10 +411,12 @@ __device__ __forceinline__ void collide(const Coef<T> &C, T h, T inv_h, T gx, T 
 // two rows in an LDS slot of two values per column (instead of nine), and
 // no populations are kept.  The values are those of the general stage bit
 // for bit: with 1 - omega = 0 its term (1 - omega) d adds an exact zero.
-template <int P, int KF, bool W1 = false> struct Stage {
+// RH: 1/h of row r-1, formed with its pressure, is kept for its collision one
+// row later instead of formed again.
+template <int P, int KF, bool W1 = false, bool G0 = false, bool RH = false> struct Stage {
   using T = typename Form<P>::T;
   static constexpr int V = Form<P>::V;
-  T h0[V + 2], h1[V + 2], h2[V + 2];  // dh of rows r, r-1, r-2 with the left/right neighbours
+  T h0[V + 2], h1[V + 2], h2[V + 2];  // dh of rows r, r-1, r-2 (row_sums)
   // per row of p: x difference p(x+1) - p(x-1) and the x-smoothed value
   // cA p(x) + cD (p(x-1) + p(x+1)), of rows r-1, r-2, r-3
   T dx1[V], dx2[V], dx3[V];
@@ -381,8 +424,48 @@ template <int P, int KF, bool W1 = false> struct Stage {
   T kn[V], kr[V];                     // kappa (or -gamma kappa) of rows r and r-1
   T an[V], ar[V];                     // -gamma/6 of rows r and r-1 (kGammaKappa)
   T jx2[V], jy2[V];                   // W1: j of row r-2, from ingest to finish
+  T ih1[RH ? V : 1], ih2[RH ? V : 1];  // 1/h of rows r-1 and r-2
   T (*hist)[9][64 * V];               // general: populations of rows r-1, r-2 [slot][l][column]
   T (*jhist)[2][64 * V];              // W1: j of rows r-1, r-2 [slot][x or y][column]
+
+  // left and right neighbours of dh of row r; kappa of row r, used by the
+  // pressure of row r at the next row
+  __device__ __forceinline__ void neighbours(const T (&kap)[V], const T (&aco)[V]) {
+    row_sums<V>(h0);
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      kr[v] = kn[v];
+      if constexpr (KF != kNoField) kn[v] = kap[v];
+      if constexpr (KF == kGammaKappa) {
+        ar[v] = an[v];
+        an[v] = aco[v];
+      }
+    }
+  }
+  // W1: j of row r takes over the LDS slot that row r-2's leaves
+  __device__ __forceinline__ void turn_j(int k, const T (&jx)[V], const T (&jy)[V], int lane) {
+    const int slot = k & 1;
+    if (k >= 4) {
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        jx2[v] = jhist[slot][0][V * lane + v];
+        jy2[v] = jhist[slot][1][V * lane + v];
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      jhist[slot][0][V * lane + v] = jx[v];
+      jhist[slot][1][V * lane + v] = jy[v];
+    }
+  }
+  // W1: ingest from the moments of row r
+  __device__ __forceinline__ void ingest(int k, const T (&dh)[V], const T (&jx)[V], const T (&jy)[V], const T (&kap)[V],
+                                         const T (&aco)[V], int lane) {
+#pragma unroll
+    for (int v = 0; v < V; ++v) h0[1 + v] = dh[v];
+    neighbours(kap, aco);
+    turn_j(k, jx, jy, lane);
+  }
 
   // kap, aco: the field values of row r (loaded with the row, load_kappa;
   // unused without a field)
@@ -395,38 +478,17 @@ template <int P, int KF, bool W1 = false> struct Stage {
       for (int l = 1; l < 9; ++l) hs += f[l][v];
       h0[1 + v] = hs;
     }
-    h0[0] = from_left(h0[V]);
-    h0[V + 1] = from_right(h0[1]);
-    // kappa of row r, used by the pressure of row r at the next row
-#pragma unroll
-    for (int v = 0; v < V; ++v) {
-      kr[v] = kn[v];
-      if constexpr (KF != kNoField) kn[v] = kap[v];
-      if constexpr (KF == kGammaKappa) {
-        ar[v] = an[v];
-        an[v] = aco[v];
-      }
-    }
+    neighbours(kap, aco);
     if constexpr (W1) {
-      // j = sum_l c_l d_l through the differences of opposite populations;
-      // row r-2's leaves the slot that row r's takes over
-      const int slot = k & 1;
-      if (k >= 4) {
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
-          jx2[v] = jhist[slot][0][V * lane + v];
-          jy2[v] = jhist[slot][1][V * lane + v];
-        }
-      }
+      T jx[V], jy[V];
 #pragma unroll
       for (int v = 0; v < V; ++v) {
-        T fv[9], jx, jy;
+        T fv[9];
 #pragma unroll
         for (int l = 0; l < 9; ++l) fv[l] = f[l][v];
-        momentum(fv, jx, jy);
-        jhist[slot][0][V * lane + v] = jx;
-        jhist[slot][1][V * lane + v] = jy;
+        momentum(fv, jx[v], jy[v]);
       }
+      turn_j(k, jx, jy, lane);
     } else {
       // row r-2 leaves the LDS slot that row r takes over
       const int slot = k & 1;
@@ -452,7 +514,9 @@ template <int P, int KF, bool W1 = false> struct Stage {
       for (int v = 0; v < V; ++v) {
         const T hc = C.href + h1[v + 1];
         const T lap6 = laplacian6(&h0[v], &h1[v], &h2[v]);
-        const T phi = disjoining(C.hstar * recip(hc), C.n_exp, C.m_exp);
+        const T ih = recip(hc);
+        if constexpr (RH) ih1[v] = ih;
+        const T phi = disjoining(C.hstar * ih, C.n_exp, C.m_exp);
         if constexpr (KF == kGammaKappa) {
           // per-site (-gamma/6, -gamma kappa), rounded at init as the scalar
           // path rounds (-gamma/6) and (-gamma) kappa
@@ -489,7 +553,10 @@ template <int P, int KF, bool W1 = false> struct Stage {
           momentum(fv, jx, jy);
         }
         const T h = C.href + dh;
-        collide<T, W1, false>(C, h, recip(h), gx, gy, dh, jx, jy, fv, pv);
+        T ih;
+        if constexpr (RH) ih = ih2[v];
+        else ih = recip(h);
+        collide<T, W1, G0>(C, h, ih, gx, gy, dh, jx, jy, fv, pv);
 #pragma unroll
         for (int l = 0; l < 9; ++l) post[l][v] = pv[l];
         hv[v] = dh;
@@ -510,6 +577,7 @@ template <int P, int KF, bool W1 = false> struct Stage {
       dx2[v] = dx1[v];
       sm3[v] = sm2[v];
       sm2[v] = sm1[v];
+      if constexpr (RH) ih2[v] = ih1[v];
     }
     return emit;
   }
@@ -552,13 +620,13 @@ constexpr int kStoreDrop = kDropBytes;
 // per-lane load branches of the general loop FP32 ran 2 % and FP16S 5 %
 // slower, in it 2 % and 5 % faster); the capture and surface tension kernels
 // would spill.
-template <int P> __device__ __forceinline__ void drop_row_stores(const StepArgs &A) {
+template <int P, int N = 12> __device__ __forceinline__ void drop_row_stores(const StepArgs &A) {
   // byte stores at distinct offsets: a store of this width occurs nowhere
   // else, so the compiler neither merges these with a row's stores nor drops
   // them as duplicates
   const rsrc_t none = make_rsrc(A.dst, 0);
 #pragma unroll
-  for (int i = 0; i < 12; ++i) __builtin_amdgcn_raw_buffer_store_b8((unsigned char)0, none, kStoreDrop + 4 * i, 0, kStorePolicy);
+  for (int i = 0; i < N; ++i) __builtin_amdgcn_raw_buffer_store_b8((unsigned char)0, none, kStoreDrop + 4 * i, 0, kStorePolicy);
 }
 
 // Stores the post-collision deviations of row y (values at the lane's own
@@ -901,31 +969,10 @@ __global__ __launch_bounds__(64, 2) void step_kernel(StepArgs A) {
   const int yend = min(y0 + A.H, A.ny);
   const int xend = min(x0 + B, A.nx);
   const int lane = threadIdx.x;
-  const int nx = A.nx, ny = A.ny;
+  const int ny = A.ny;
   const size_t rowB = (size_t)A.nblk * RB;
 
-  Lane<P> L;
-  const int a = x0 - HX + V * lane;  // first (unwrapped) column of this lane
-#pragma unroll
-  for (int v = 0; v < V; ++v) {
-    L.col[v] = wrap(a + v, nx);
-    const int blk = L.col[v] / B;
-    const int pos = L.col[v] - blk * B;
-    L.oe[v] = blk * RB + pos * ES;
-    L.oc[v] = blk * cap_record_bytes<P>() + pos * ES;
-    L.o16[v] = blk * RB + pos * 2;
-    L.out[v] = (a + v >= x0) && (a + v < xend);
-  }
-  L.vec = true;
-  L.vecp = true;
-  if constexpr (V == 2) {
-    L.vec = (L.col[1] == L.col[0] + 1) && (L.col[0] / B == L.col[1] / B) && ((L.col[0] & 1) == 0);
-    L.vecp = (L.col[1] == L.col[0] + 1) && ((L.col[0] & 1) == 0);
-  }
-  L.pair = L.out[0] && L.out[V - 1] && L.vec;
-  L.allvec = __all(L.vec);
-  L.allvecp = __all(L.vecp);
-  L.fast_store = __all(L.pair || (!L.out[0] && !L.out[V - 1]));
+  const Lane<P> L(x0 - HX + V * lane, x0, xend, A.nx);
   const Coef<T> C(A);
 
   Stage<P, KF, W1> S0, S1, S2;

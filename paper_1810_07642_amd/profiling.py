@@ -36,20 +36,22 @@ CSRC = os.path.join(PKG, "csrc")
 
 # Sources a kernel's traffic depends on: the kernel and the launch plan that
 # sets its tiles (hence its halo re-reads).
-STEP_SOURCES = [os.path.join(CSRC, f) for f in ("step.h", "step_form.hip", "fwd.hip", "device.h", "api.hip")]
+STEP_SOURCES = [os.path.join(CSRC, f) for f in ("step.h", "step_form.hip", "march.h", "march_form.hip",
+                                                  "march.hip", "fwd.hip", "device.h", "api.hip")]
 ADJ_SOURCES = [os.path.join(CSRC, f) for f in ("adj.hip", "device.h", "api.hip")]
 
 N4096 = 4096 * 4096
-# Algorithmic bytes per site of one pass of the fused two-step kernel: every
-# record read and written once (9 populations) plus the kappa field read once.
-STEP_BYTES = {"fp64": (80, 72), "fp32": (40, 36), "fp16s": (24, 20)}  # (read, write) per site
-# The kernel the benchmark workload (tau = 1, 4096^2) runs per form and the
-# steps one launch of it advances: three fused steps of the omega = 1 stages
-# in FP64 and FP32, two in FP16S (g = 0).
-STEP_KERNEL = {"fp64": ("step_kernel<0, 1, false, 3, false, true>", 3),
-               "fp32": ("step_kernel<1, 1, false, 3, false, true>", 3),
+# Algorithmic bytes per site of one pass: the three moments (FP64, FP32: a pass
+# between two others) or the record (FP16S) read and written once, plus the kappa
+# field read once.
+STEP_BYTES = {"fp64": (32, 24), "fp32": (16, 12), "fp16s": (24, 20)}  # (read, write) per site
+# The kernel the benchmark workload (tau = 1, 4096^2, g = 0) runs per form and the
+# steps one launch of it advances: three steps from moments to moments in FP64
+# and FP32, two in FP16S.
+STEP_KERNEL = {"fp64": ("march_kernel<0, 1, false, 3, true, true, true, 3, 3>", 3),
+               "fp32": ("march_kernel<1, 1, false, 3, true, true, true, 3, 6>", 3),
                "fp16s": ("step_kernel<2, 1, false, 2, true, true>", 2)}
-PROFILE_STEPS = 24  # a multiple of 2 and of 3: whole passes of the kernel
+PROFILE_STEPS = 26  # a first pass of two steps and eight of three; thirteen of two (FP16S)
 # The two-step reverse pass of the benchmark workload (tau = 1: the adjoint
 # between steps as three fields per site), FP32: fields 12 + two captures 24 +
 # kappa 4 + g_kappa 8 read; fields 12 + g_kappa 8 written.  (The general pass
@@ -300,9 +302,10 @@ def main(argv=None):
             f"{args.storage.upper()} storage, kappa field, {spp} time steps per launch, omega = 1 stages",
             re.escape(kname), args.fetch, args.write,
             r * N4096, w * N4096, spp, STEP_SOURCES, cmds, sq_dir=args.sq, trace_dir=args.trace,
-            alg_desc=f"records read and written once and the kappa field read once ({r}/{w} B/site)",
+            alg_desc=f"{'records' if args.storage == 'fp16s' else 'moments'} read and written once and the kappa field "
+                     f"read once ({r}/{w} B/site)",
             notes=[f"`bench.py --profile-steps {PROFILE_STEPS}` runs {PROFILE_STEPS} steps "
-                   f"({PROFILE_STEPS // spp} launches) of the benchmark workload, a record copy of one population "
+                   "of the benchmark workload, a record copy of one population "
                    "buffer (tflbm_state_save) and a 1 GiB runtime copy that calibrates the counters."])
     else:
         cmds = [f"rocprofv3 --pmc {c} --output-format csv -d <repo>/gpurun_out/adj_{c} -o run -- "
