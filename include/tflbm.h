@@ -142,6 +142,7 @@ int tflbm_check_params(const tflbm_params *p);
  * with at most n steps per pass; by default on lattices where it is faster
  * than the marching kernels, unless one of the variables above asks for a
  * shape of theirs) and TFLBM_BLOCK_SHAPE (its tile shape),
+ * TFLBM_ADJ_BLOCK and TFLBM_ADJ_BLOCK_SHAPE (the same for tflbm_adj_steps),
  * TFLBM_MARCH=0, 2 or 3 (read at tflbm_init: with tau = 1, whether the marching
  * kernels' passes of a call hand over moments instead of populations, and two or
  * three steps per such pass; by default by lattice size; the same bits) and
@@ -313,8 +314,9 @@ int tflbm_adj_step(tflbm_sim *sim, void *d_adj, const void *d_capture_t, tflbm_s
  * nsteps captures must be there).  On lattices that fill the GPU, two
  * steps run per pass over the lattice, the adjoint of step t feeding that of
  * step t-1 on chip, which halves the adjoint and kappa-gradient traffic; on
- * smaller ones the steps run singly.  The result is bit for bit that of the
- * single steps either way.  nsteps = 0 does nothing; EINVAL for nsteps < 0 or
+ * small ones a block kernel runs several steps of a tile per launch; else the
+ * steps run singly.  The result is bit for bit that of the single steps in
+ * every case.  nsteps = 0 does nothing; EINVAL for nsteps < 0 or
  * a NULL pointer, ESTATE before tflbm_adj_seed. */
 int tflbm_adj_steps(tflbm_sim *sim, void *d_adj, const void *d_capture, int64_t nsteps, tflbm_stream_t stream);
 

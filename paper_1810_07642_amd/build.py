@@ -21,7 +21,9 @@ UNITS += [(f"block_{form}_{'w1' if w1 else 'general'}", "block_form.hip", [f"-DS
 UNITS = [(f"march_{form}_{field}", "march_form.hip", [f"-DSTEP_FORM={P}", f"-DMARCH_FIELD={F}"])
          for form, P in (("f32", "kF32"), ("f64", "kF64"))
          for field, F in (("kappa", "kKappa"), ("uniform", "kNoField"))] + UNITS
-UNITS += [(s[:-4], s, []) for s in ("adj.hip", "fwd.hip", "block.hip", "march.hip", "api.hip", "diag.hip", "noalloc.hip")]
+UNITS += [(f"adj_block_{T}_{'w1' if w1 else 'general'}", "adj_block_form.hip", [f"-DADJ_TYPE={T}", f"-DSTEP_W1={w1}"])
+          for T in ("float", "double") for w1 in (1, 0)]
+UNITS += [(s[:-4], s, []) for s in ("adj.hip", "fwd.hip", "block.hip", "march.hip", "adj_block.hip", "api.hip", "diag.hip", "noalloc.hip")]
 SOURCES = sorted({src for _, src, _ in UNITS})
 OBJ = os.path.join(PKG, "_build")
 ARCH = "gfx950"

@@ -164,6 +164,10 @@ void plan_launches(tflbm_sim *s) {
   bool march = s->fuse != 0;
   for (const char *v : {"TFLBM_ROWS", "TFLBM_ROWS2", "TFLBM_ROWS3"}) march = march || std::getenv(v) != nullptr;
   if (march || !plan_block(s, s->block)) s->block = BlockPlan();
+  // the reverse block kernel, likewise
+  march = s->adj_fuse != 0;
+  for (const char *v : {"TFLBM_ADJ_ROWS", "TFLBM_ADJ_ROWS2"}) march = march || std::getenv(v) != nullptr;
+  if (march || !plan_adj_block(s, s->adj_block)) s->adj_block = BlockPlan();
   s->graphs = (int64_t)s->p.nx * ny <= kGraphMaxSites;
   if (const char *e = std::getenv("TFLBM_GRAPH")) s->graphs = std::atoi(e) != 0;
 }

@@ -56,16 +56,6 @@ template <> struct BlockShapes<kF64, true> {
 template <> struct BlockShapes<kF64, false> {
   static constexpr BlockShape list[] = {{1, 16, true}, {2, 12, true}};
 };
-inline BlockShape block_shape(int prec, bool w1, int i) {
-  return prec == kF64 ? (w1 ? BlockShapes<kF64, true>::list[i] : BlockShapes<kF64, false>::list[i])
-                      : (w1 ? BlockShapes<kF32, true>::list[i] : BlockShapes<kF32, false>::list[i]);
-}
-
-// Whether the n tile rows from r0 on, of `rows` in use, hold a row whose
-// pressure the stored rows still depend on in step s of a pass.
-__host__ __device__ __forceinline__ bool block_active(int r0, int n, int rows, int s) {
-  return r0 + n > 3 * s + 1 && r0 < rows - 3 * s - 1;
-}
 
 template <int P, bool W1, bool GF, bool G0, bool CAP, int R, int NW>
 __global__ __launch_bounds__(64 * NW) void block_kernel(BlockArgs A, Coef<typename Form<P>::T> C) {

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "device.h"
+#include "tiles.h"
 
 namespace tflbm {
 
@@ -54,14 +55,6 @@ struct BlockArgs {
   float ksign;        // the sign of phi(h) = (h_*/h)^9 - (h_*/h)^3: -1 for the exponents (3, 9)
 };
 
-struct BlockShape {
-  int r, nw;   // rows per wavefront, wavefronts per workgroup
-  bool pairs;  // the shape takes a surface tension field
-};
-// A block plan: index of the shape and most steps per pass (0: no plan).
-struct BlockPlan {
-  int shape = 0, ns = 0;
-};
 // ns steps of every tile in one launch (block.h).
 hipError_t launch_block(int prec, bool w1, int shape, const BlockArgs &A, hipStream_t s);
 

@@ -49,6 +49,7 @@ struct tflbm_sim {
   int adj_rows = 0, adj_ntiles = 0, adj_per_xcd = 0;      // one step per pass
   int adj2_rows = 0, adj2_ntiles = 0, adj2_per_xcd = 0;   // two steps per pass
   int adj_fuse = 0;       // reverse steps per pass: 1, 2 (when possible), 0 = 2 if adj_fuse_fits
+  tflbm::BlockPlan adj_block;  // lattices too small for the marching reverse kernels: the reverse block kernel
   bool adj_fuse_fits = false;  // the lattice fills the GPU with two-step tiles
   mutable std::string last_error;
 };
@@ -76,6 +77,8 @@ void plan_launches(tflbm_sim *s);
 // and its launch shape for a pass of ns steps.
 bool plan_block(const tflbm_sim *s, BlockPlan &best);
 void shape_block(const tflbm_sim *s, int shape, int ns, BlockArgs &A);
+// The same for the reverse block kernel.
+bool plan_adj_block(const tflbm_sim *s, BlockPlan &best);
 
 // Passes that hand over moments: their plan, and the split of a call of nsteps
 // steps into `passes` passes, the first of two steps, `threes` of the others of

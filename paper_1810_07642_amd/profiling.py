@@ -38,7 +38,7 @@ CSRC = os.path.join(PKG, "csrc")
 # sets its tiles (hence its halo re-reads).
 STEP_SOURCES = [os.path.join(CSRC, f) for f in ("step.h", "step_form.hip", "march.h", "march_form.hip",
                                                   "march.hip", "fwd.hip", "device.h", "api.hip")]
-ADJ_SOURCES = [os.path.join(CSRC, f) for f in ("adj.hip", "device.h", "api.hip")]
+ADJ_SOURCES = [os.path.join(CSRC, f) for f in ("adj.h", "adj.hip", "device.h", "api.hip")]
 
 N4096 = 4096 * 4096
 # Algorithmic bytes per site of one pass: the three moments (FP64, FP32: a pass
