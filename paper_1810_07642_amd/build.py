@@ -17,7 +17,7 @@ LIB = os.path.join(PKG, "libtflbm.so")
 UNITS = [(f"step_{form}_{'w1' if w1 else 'general'}", "step_form.hip", [f"-DSTEP_FORM={P}", f"-DSTEP_W1={w1}"])
          for form, P in (("f16s", "kF16S"), ("f32", "kF32"), ("f64", "kF64")) for w1 in (1, 0)]
 UNITS += [(f"block_{form}_{'w1' if w1 else 'general'}", "block_form.hip", [f"-DSTEP_FORM={P}", f"-DSTEP_W1={w1}"])
-          for form, P in (("f32", "kF32"), ("f64", "kF64")) for w1 in (1, 0)]
+          for form, P in (("f32", "kF32"), ("f64", "kF64"), ("f16s", "kF16S")) for w1 in (1, 0)]
 UNITS = [(f"march_{form}_{field}", "march_form.hip", [f"-DSTEP_FORM={P}", f"-DMARCH_FIELD={F}"])
          for form, P in (("f32", "kF32"), ("f64", "kF64"))
          for field, F in (("kappa", "kKappa"), ("uniform", "kNoField"))] + UNITS

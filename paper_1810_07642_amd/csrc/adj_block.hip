@@ -34,8 +34,8 @@ bool plan_adj_block(const tflbm_sim *s, BlockPlan &best) {
     return false;
   const TileModel &m = kModel[p.prec == kF64 ? 0 : 1][s->w1 ? 1 : 0];
   bool forced = false;
-  const double t = best_plan(m, shapes_of(p.prec, s->w1), 2, p.nx, p.ny, false, "TFLBM_ADJ_BLOCK", "TFLBM_ADJ_BLOCK_SHAPE",
-                             best, forced);
+  const double t = best_plan(m, shapes_of(p.prec, s->w1), 2, p.nx, p.ny, 0, false, "TFLBM_ADJ_BLOCK",
+                             "TFLBM_ADJ_BLOCK_SHAPE", best, forced);
   if (best.ns == 0) return false;
   if (forced) return true;
   return (int64_t)p.nx * p.ny <= kAdjBlockMaxSites && t < 0.9 * m.march((double)s->adj_nstrips * p.ny, m.march2);

@@ -23,7 +23,8 @@
 // chain of rows; here it is ns times three exchanges.  Measured (us per step,
 // marching / block, step graphs on): FP32 at omega = 1 64^2 4.6 / 2.2, 256^2
 // 5.3 / 2.5, 512^2 9.1 / 4.1, 1024x512 11.2 / 6.3, 1024^2 14.9 / 10.8; FP32
-// general 256^2 5.8 / 2.8, 512^2 9.0 / 4.7; FP64 at omega = 1 64^2 3.8 / 2.7,
+// general 256^2 5.8 / 2.8, 512^2 9.0 / 4.7; FP16S at omega = 1 128^2 5.2 / 2.6,
+// 512^2 9.1 / 4.8, 901x641 (odd width) 24.0 / 7.7; FP64 at omega = 1 64^2 3.8 / 2.7,
 // 512^2 10.2 / 5.2; FP64 general 64^2 4.0 / 3.1, 384^2 8.4 / 4.6, 512^2 10.8 /
 // 9.4 (its tiles hold two rows per wavefront at most: 2 x 9 FP64 populations).
 // What is left of a pass: about 2.5 us of launch, 1.5-2 us until the state is
@@ -50,6 +51,12 @@ template <> struct BlockShapes<kF32, true> {
 template <> struct BlockShapes<kF32, false> {
   static constexpr BlockShape list[] = {{2, 16, true}, {3, 8, true}};
 };
+template <> struct BlockShapes<kF16S, true> {
+  static constexpr BlockShape list[] = {{2, 16, true}, {3, 16, true}, {5, 16, true}};
+};
+template <> struct BlockShapes<kF16S, false> {
+  static constexpr BlockShape list[] = {{2, 16, true}, {3, 8, true}};
+};
 template <> struct BlockShapes<kF64, true> {
   static constexpr BlockShape list[] = {{2, 16, true}, {3, 12, true}, {4, 12, false}};
 };
@@ -60,8 +67,8 @@ template <> struct BlockShapes<kF64, false> {
 template <int P, bool W1, bool GF, bool G0, bool CAP, int R, int NW>
 __global__ __launch_bounds__(64 * NW) void block_kernel(BlockArgs A, Coef<typename Form<P>::T> C) {
   using T = typename Form<P>::T;
-  static_assert(P == kF64 || P == kF32, "storage forms with one element type");
-  constexpr int B = Form<P>::B, RB = Form<P>::RB, ES = sizeof(T), SEG = Form<P>::SEG, CRB = cap_record_bytes<P>();
+  constexpr bool F16 = P == kF16S;
+  constexpr int B = Form<P>::B, RB = Form<P>::RB, ES = sizeof(T), SEG = B * ES, CRB = cap_record_bytes<P>();
   // dh and p of a wavefront's first and last row; of the populations, those
   // that leave it downwards (2, 3, 4 of its last row) and upwards (6, 7, 8 of
   // its first row)
@@ -91,7 +98,7 @@ __global__ __launch_bounds__(64 * NW) void block_kernel(BlockArgs A, Coef<typena
   // wavefront's first row.  A tile reaches less than one lattice beyond it
   // unless the lattice is smaller than a tile: loops of no or one turn, where a
   // division would cost every launch some twenty instructions per wavefront.
-  const int a = x0 - halo + lane;
+  const int a = x0 - A.halo_x + lane;
   int col[3], y = y0 - halo + r0;
   col[0] = a - 1;
   while (col[0] < 0) col[0] += nx;
@@ -103,8 +110,9 @@ __global__ __launch_bounds__(64 * NW) void block_kernel(BlockArgs A, Coef<typena
   int off[3];  // byte offsets of the three columns in a row of records
 #pragma unroll
   for (int j = 0; j < 3; ++j) off[j] = col[j] / B * RB + col[j] % B * ES;
+  const int off16 = col[1] / B * RB + col[1] % B * 2;  // FP16S: of column a in an FP16 segment
   const bool out = a >= x0 && a < xend;  // a column of the tile's own
-  const int off_st = out ? off[1] : kStoreDrop;
+  const int off_st = out ? off[1] : kStoreDrop, off_st16 = out ? off16 : kStoreDrop;
   // Every array is one buffer resource, its rows scalar byte offsets (the
   // library runs this kernel on arrays under 2 GiB only): building a resource
   // per row costs each wavefront some twenty scalar instructions a row (8 % of
@@ -117,6 +125,14 @@ __global__ __launch_bounds__(64 * NW) void block_kernel(BlockArgs A, Coef<typena
     if constexpr (P == kF64) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, o, row, kStorePolicy);
     else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, o, row, kStorePolicy);
   };
+  auto ld16 = [](rsrc_t r, int o, int row) -> unsigned short {
+    return __builtin_amdgcn_raw_buffer_load_b16(r, o, row, kLoadPolicy);
+  };
+  auto st16 = [](rsrc_t r, int o, int row, unsigned int v) {
+    __builtin_amdgcn_raw_buffer_store_b16((unsigned short)v, r, o, row, kStorePolicy);
+  };
+  // FP16S keeps j in the two halves of four FP16 segments
+  constexpr int kHalf[2][2] = {{1, 5}, {2, 3}};
   // the next row and its offset in an array of `pitch` bytes per row
   auto next = [&](int &yr, int &o, int pitch) {
     ++yr;
@@ -140,13 +156,66 @@ __global__ __launch_bounds__(64 * NW) void block_kernel(BlockArgs A, Coef<typena
       if (in_mom) {
         const int k = W1 ? i : 0;
         dh[i] = ld(src, off[1], o);
-        jx[k] = ld(src, off[1] + SEG, o);
-        jy[k] = ld(src, off[1] + 2 * SEG, o);
-      } else {
+        if constexpr (F16) {
+          T *const j[2] = {&jx[k], &jy[k]};
+#pragma unroll
+          for (int d = 0; d < 2; ++d) {
+            const unsigned int hi = ld16(src, off16 + seg_offset<P>(kHalf[d][0]), o),
+                               lo = ld16(src, off16 + seg_offset<P>(kHalf[d][1]), o);
+            *j[d] = __uint_as_float(hi << 16 | lo);
+          }
+        } else {
+          jx[k] = ld(src, off[1] + SEG, o);
+          jy[k] = ld(src, off[1] + 2 * SEG, o);
+        }
+      } else if constexpr (!F16) {
 #pragma unroll
         for (int l = 0; l < 9; ++l) f[i][l] = ld(src, off[1 - kCx[l]] + seg_offset<P>(l), o);
       }
       next(yr, o, rowB);
+    }
+    if constexpr (F16) {
+      if (!in_mom) {
+        // decode as fp16s_decode does: the moving populations of a row with the
+        // rest equilibrium of their source rows, the implied rest population from
+        // those the row emitted into the rows around it; then the x shift
+        const int last = (ny - 1) * rowB;
+        T sh[R + 2], q[R + 2][9];
+        o = y == 0 ? last : (y - 1) * rowB;
+        yr = y == 0 ? ny - 1 : y - 1;
+#pragma unroll
+        for (int i = 0; i < R + 2; ++i) {
+          sh[i] = ld(src, off[1], o);
+#pragma unroll
+          for (int l = 1; l < 9; ++l)
+            if ((i >= 1 && i <= R) || (i == 0 && l >= 6) || (i == R + 1 && l >= 2 && l <= 4))
+              q[i][l] = dec16(__ushort_as_half(ld16(src, off16 + seg_offset<P>(l), o)), A.s.qinv);
+          next(yr, o, rowB);
+        }
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+          T t[9], d[9];
+          t[0] = 0.0f;
+          if constexpr (G0) {
+#pragma unroll
+            for (int l = 1; l < 9; ++l) {
+              d[l] = q[1 + i][l];
+              t[l] = q[1 + i + kCy[l]][l];
+            }
+          } else {
+            const float h2 = 2.0f * C.href;
+            const Rest16 e[3] = {rest16(sh[i], C.g, h2), rest16(sh[1 + i], C.g, h2), rest16(sh[2 + i], C.g, h2)};
+#pragma unroll
+            for (int l = 1; l < 9; ++l) {
+              d[l] = rest16_l(e[1 - kCy[l]], l) + q[1 + i][l];
+              t[l] = rest16_l(e[1], l) + q[1 + i + kCy[l]][l];
+            }
+          }
+          d[0] = rest16_d0(sh[1 + i], t);
+#pragma unroll
+          for (int l = 0; l < 9; ++l) shift_x<T, 1>(l, &d[l], &f[i][l]);
+        }
+      }
     }
     const T sg = (T)A.ksign;
     if (GF || A.kf == kKappa) {
@@ -255,6 +324,20 @@ __global__ __launch_bounds__(64 * NW) void block_kernel(BlockArgs A, Coef<typena
       }
     }
     if (s + 1 == ns && !(W1 && A.out_mom)) break;
+    if constexpr (F16) {
+      if (act) {
+#pragma unroll
+        for (int i = 0; i < R; ++i) {  // as if stored and loaded again
+          T pv[9][1];
+          const T hv[1] = {dh[i]};
+#pragma unroll
+          for (int l = 0; l < 9; ++l) pv[l][0] = f[i][l];
+          fp16s_roundtrip<1, G0>(pv, hv, A.s);
+#pragma unroll
+          for (int l = 0; l < 9; ++l) f[i][l] = pv[l][0];
+        }
+      }
+    }
     if (act) {
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
@@ -299,12 +382,33 @@ __global__ __launch_bounds__(64 * NW) void block_kernel(BlockArgs A, Coef<typena
         if (W1 && A.out_mom) {
           const int k = W1 ? i : 0;
           st(dst, off_st, o, dh[i]);
-          st(dst, off_st + SEG, o, jx[k]);
-          st(dst, off_st + 2 * SEG, o, jy[k]);
+          if constexpr (F16) {
+            const T j[2] = {jx[k], jy[k]};
+#pragma unroll
+            for (int d = 0; d < 2; ++d) {
+              const unsigned int u = __float_as_uint(j[d]);
+              st16(dst, off_st16 + seg_offset<P>(kHalf[d][0]), o, u >> 16);
+              st16(dst, off_st16 + seg_offset<P>(kHalf[d][1]), o, u & 0xffffu);
+            }
+          } else {
+            st(dst, off_st + SEG, o, jx[k]);
+            st(dst, off_st + 2 * SEG, o, jy[k]);
+          }
         } else {
           const int rd[3] = {o == 0 ? last : o - rowB, o, o == last ? 0 : o + rowB};  // by c_ly + 1
+          if constexpr (F16) {
+            st(dst, off_st, o, dh[i]);
+            const Rest16 e = rest16(dh[i], C.g, 2.0f * C.href);
 #pragma unroll
-          for (int l = 0; l < 9; ++l) st(dst, off_st + seg_offset<P>(l), rd[kCy[l] + 1], f[i][l]);
+            for (int l = 1; l < 9; ++l) {
+              const float d = G0 ? f[i][l] : f[i][l] - rest16_l(e, l);
+              st16(dst, off_st16 + seg_offset<P>(l), rd[kCy[l] + 1],
+                   __builtin_bit_cast(unsigned short, (_Float16)(d * A.s.qscale)));
+            }
+          } else {
+#pragma unroll
+            for (int l = 0; l < 9; ++l) st(dst, off_st + seg_offset<P>(l), rd[kCy[l] + 1], f[i][l]);
+          }
         }
       }
       next(yr, o, rowB);

@@ -13,9 +13,11 @@ extern template hipError_t launch_block_form<kF64, false>(int, const BlockArgs &
 extern template hipError_t launch_block_form<kF64, true>(int, const BlockArgs &, hipStream_t);
 extern template hipError_t launch_block_form<kF32, false>(int, const BlockArgs &, hipStream_t);
 extern template hipError_t launch_block_form<kF32, true>(int, const BlockArgs &, hipStream_t);
+extern template hipError_t launch_block_form<kF16S, false>(int, const BlockArgs &, hipStream_t);
+extern template hipError_t launch_block_form<kF16S, true>(int, const BlockArgs &, hipStream_t);
 
-double best_plan(const TileModel &m, const BlockShape *shapes, int n, int nx, int ny, bool pairs, const char *env,
-                 const char *env_shape, BlockPlan &best, bool &forced) {
+double best_plan(const TileModel &m, const BlockShape *shapes, int n, int nx, int ny, int extra, bool pairs,
+                 const char *env, const char *env_shape, BlockPlan &best, bool &forced) {
   best = BlockPlan();
   forced = false;
   int ns_min = 1, ns_max = 9, only = -1;
@@ -30,7 +32,7 @@ double best_plan(const TileModel &m, const BlockShape *shapes, int n, int nx, in
   for (int i = 0; i < n; ++i) {
     if ((only >= 0 && i != only) || (pairs && !shapes[i].pairs)) continue;
     for (int ns = ns_min; ns <= ns_max; ++ns) {
-      const Tiles t(nx, ny, shapes[i], ns);
+      const Tiles t(nx, ny, shapes[i], ns, extra);
       if (!t.fits) break;
       const double dt = m.pass(t, shapes[i], ns) / ns;
       if (dt < best_t) {
@@ -44,13 +46,19 @@ double best_plan(const TileModel &m, const BlockShape *shapes, int n, int nx, in
 }
 
 // Fitted to 17 lattices of 64^2 to 1200^2 sites, 4 to 13 shapes and 2 to 8
-// steps: what it picks is within 1 % (FP64) to 7 % (FP32, general stages) of
-// the fastest measured, on average.  [FP64, FP32][general, omega = 1]
-static const TileModel kModel[2][2] = {
+// steps: what it picks is within 1 % (FP64) to 6 % (FP16S) of the fastest
+// measured, on average.  [FP64, FP32, FP16S][general, omega = 1]
+static const TileModel kModel[3][2] = {
     {{1.35, 0.00, 0.263, 0.0445, 0, 1.0, 4.0, 1.9e-3, 0.72e-3}, {1.14, 0.44, 0.107, 0.0682, 0, 1.0, 3.8, 1.8e-3, 0.50e-3}},
-    {{2.99, 0.21, 0.050, 0.0693, 0, 0.74, 5.0, 1.6e-3, 0.95e-3}, {2.98, 0.25, 0.034, 0.0562, 0, 0.58, 4.6, 1.8e-3, 0.75e-3}}};
+    {{1.22, 1.01, 0.158, 0.0048, 0, 0.71, 5.0, 1.6e-3, 0.95e-3}, {2.98, 0.25, 0.034, 0.0562, 0, 0.58, 4.6, 1.8e-3, 0.75e-3}},
+    {{1.01, 0.88, 0.099, 0.0564, 0, 0.80, 5.2, 1.6e-3, 0.75e-3}, {0.61, 0.86, 0.074, 0.0599, 0, 0.83, 5.1, 1.5e-3, 0.75e-3}}};
+// The marching FP16S kernels on lattices of odd width: their edge strips load
+// misaligned column pairs half by half (us per step, 1500 / 1501 columns 21.3 /
+// 49.7, 2000 / 2001 32.9 / 73.9), which the block kernel's lanes of one column
+// never do (2001^2 46).
+constexpr double kOddF16 = 2.3;
 // march2 where the marching passes hand over moments (march.h): FP64, FP32.
-constexpr double kMarchMoments[2] = {0.28e-3, 0.385e-3};
+constexpr double kMarchMoments[3] = {0.28e-3, 0.385e-3, 0};
 // Largest lattice the model was fitted to.
 constexpr int64_t kBlockMaxSites = 1500000;
 
@@ -60,40 +68,49 @@ static const BlockShape *shapes_of(int prec, bool w1, int &n) {
     return (const BlockShape *)list;
   };
   if (prec == kF64) return w1 ? of(BlockShapes<kF64, true>::list) : of(BlockShapes<kF64, false>::list);
+  if (prec == kF16S) return w1 ? of(BlockShapes<kF16S, true>::list) : of(BlockShapes<kF16S, false>::list);
   return w1 ? of(BlockShapes<kF32, true>::list) : of(BlockShapes<kF32, false>::list);
 }
 
+// FP16S loses a column per side more: it decodes its populations where they are
+// stored and shifts them into place.
+static int extra_columns(int prec) { return prec == kF16S ? 1 : 0; }
+
 // False where the marching kernels are faster, or the block kernel does not
-// serve the handle: FP16S, disjoining exponents other than (9, 3) and (3, 9),
-// arrays its 32-bit row offsets do not reach.
+// serve the handle: disjoining exponents other than (9, 3) and (3, 9), arrays its 32-bit row offsets do not reach.
 bool plan_block(const tflbm_sim *s, BlockPlan &best) {
   best = BlockPlan();
   const tflbm_params &p = s->p;
   const bool exps = (p.n_exp == 9 && p.m_exp == 3) || (p.n_exp == 3 && p.m_exp == 9);
-  if (p.prec == kF16S || !exps) return false;
+  if (!exps) return false;
   if (s->pop_bytes >= (size_t)kDropBytes || s->kf_bytes >= (size_t)kDropBytes ||
       tflbm_capture_bytes(s) >= (size_t)kDropBytes)
     return false;
-  const int f = p.prec == kF64 ? 0 : 1;
+  const int f = p.prec == kF64 ? 0 : (p.prec == kF32 ? 1 : 2);
   const TileModel &m = kModel[f][s->w1 ? 1 : 0];
   int n = 0;
   const BlockShape *shapes = shapes_of(p.prec, s->w1, n);
   bool forced = false;
-  const double t = best_plan(m, shapes, n, p.nx, p.ny, s->kfield == kGammaKappa, "TFLBM_BLOCK", "TFLBM_BLOCK_SHAPE", best,
-                             forced);
+  const double t = best_plan(m, shapes, n, p.nx, p.ny, extra_columns(p.prec), s->kfield == kGammaKappa, "TFLBM_BLOCK",
+                             "TFLBM_BLOCK_SHAPE", best, forced);
   if (best.ns == 0) return false;
   if (forced) return true;
-  if ((int64_t)p.nx * p.ny > kBlockMaxSites) return false;
+  const bool odd = p.prec == kF16S && (p.nx & 1) != 0;
+  if (!odd && (int64_t)p.nx * p.ny > kBlockMaxSites) return false;
   // (a tie stays with the marching kernels)
-  return t < 0.9 * m.march((double)s->nstrips * p.ny, s->march_ns > 0 ? kMarchMoments[f] : m.march2);
+  const double march = m.march((double)s->nstrips * p.ny, s->march_ns > 0 ? kMarchMoments[f] : m.march2);
+  // and so does a surface tension field where that is near (FP32, general stages,
+  // 808x1306: 25 us per step against 16)
+  return t < (s->kfield == kGammaKappa ? 0.75 : 0.9) * march * (odd ? kOddF16 : 1.0);
 }
 
 // Launch shape of a pass of ns steps of a plan.
 void shape_block(const tflbm_sim *s, int shape, int ns, BlockArgs &A) {
   int n = 0;
-  const Tiles t(s->p.nx, s->p.ny, shapes_of(s->p.prec, s->w1, n)[shape], ns);
+  const Tiles t(s->p.nx, s->p.ny, shapes_of(s->p.prec, s->w1, n)[shape], ns, extra_columns(s->p.prec));
   A.ns = ns;
   A.halo = t.halo;
+  A.halo_x = t.halo_x;
   A.bw = t.bw;
   A.bh = t.bh;
   A.ntx = t.ntx;
@@ -108,7 +125,7 @@ hipError_t launch_block(int prec, bool w1, int shape, const BlockArgs &A, hipStr
   switch (prec) {
     case kF64: return w1 ? launch_block_form<kF64, true>(shape, A, s) : launch_block_form<kF64, false>(shape, A, s);
     case kF32: return w1 ? launch_block_form<kF32, true>(shape, A, s) : launch_block_form<kF32, false>(shape, A, s);
-    default: return hipErrorInvalidValue;
+    default: return w1 ? launch_block_form<kF16S, true>(shape, A, s) : launch_block_form<kF16S, false>(shape, A, s);
   }
 }
 

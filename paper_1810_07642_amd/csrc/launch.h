@@ -45,7 +45,7 @@ hipError_t launch_copy(const void *src, void *dst, size_t bytes, hipStream_t s);
 struct BlockArgs {
   StepArgs s;
   int ns;             // time steps of this pass
-  int halo;           // columns and rows the tile loses per side
+  int halo, halo_x;   // rows and columns the tile loses per side
   int bw, bh;         // output columns and rows of a tile
   int ntx;            // tiles per row of tiles
   unsigned inv_ntx;   // 2^32 / ntx rounded down, at most 2^32 - 1

@@ -93,14 +93,10 @@ template <int P, int KF, bool CAP, int NS, bool MO, bool G0, bool PAD> struct Ma
       for (int i = 0; i < 3; ++i) st_f32x2(row, o + i * SEG, m[i][0], m[i][1]);
     } else {
 #pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        if (L.pair) {
-          st_f32x2(row, om[0] + i * SEG, m[i][0], m[i][1]);
-        } else {
+      for (int v = 0; v < V; ++v) {
+        const int o = L.out[v] ? om[v] : kStoreDrop;
 #pragma unroll
-          for (int v = 0; v < V; ++v)
-            if (L.out[v]) st_t(row, om[v] + i * SEG, m[i][v]);
-        }
+        for (int i = 0; i < 3; ++i) st_t(row, o + i * SEG, m[i][v]);
       }
     }
     // the padding, so that the group's last line is written whole
@@ -201,7 +197,7 @@ __global__ __launch_bounds__(64, 2) void march_kernel(StepArgs A) {
         const int o0 = MI ? m.om[0] : L.oe[0], o1 = MI ? m.om[V - 1] : L.oe[V - 1];
         if constexpr (P == kF64) {
           out[i] = ld_f64(row, o0 + seg);
-        } else if (AV || L.allvec || L.vec) {
+        } else if (AV || L.allvec) {
           out[i] = __builtin_bit_cast(Word, __builtin_amdgcn_raw_buffer_load_b64(row, o0 + seg, 0, kLoadPolicy));
         } else {
           const u32x2 w = {__builtin_amdgcn_raw_buffer_load_b32(row, o0 + seg, 0, kLoadPolicy),
@@ -278,12 +274,13 @@ __global__ __launch_bounds__(64, 2) void march_kernel(StepArgs A) {
       }
     };
     using std::integral_constant;
+    constexpr int UU = P == kF64 || AV || U < 3 ? U : 3;  // (the general FP32 loop would spill)
     int k = 0;
     for (; k + PF <= K && k < KST; k += PF) group(integral_constant<int, PF>(), k);
-    if constexpr (U > PF) {
-      for (; k + U <= K; k += U) {
+    if constexpr (UU > PF && UU % PF == 0) {
+      for (; k + UU <= K; k += UU) {
         __builtin_assume(k >= KST);
-        group(integral_constant<int, U>(), k);
+        group(integral_constant<int, UU>(), k);
       }
     }
     for (; k + PF <= K; k += PF) {

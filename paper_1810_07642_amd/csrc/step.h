@@ -126,7 +126,10 @@ template <int P> struct Lane {
 // Loads the stored deviations of all nine populations of one row.  Strips
 // whose lanes all hold aligned column pairs (every strip of a lattice whose
 // width is a multiple of the record size, and all interior strips otherwise)
-// take the wave-uniform vector path with no per-lane branches.
+// load pairs, the others (at the lattice's edges) every column by itself.  In
+// FP32 that goes without a branch per lane, whose two load shapes the compiler
+// would merge right behind the loads, waiting for them: all tiles run at once,
+// so the edge strips' tiles set the time.
 template <int P>
 __device__ __forceinline__ void load_row(rsrc_t row, const Lane<P> &L, typename Form<P>::T (&out)[9][Form<P>::V],
                                          const StepArgs &A) {
@@ -155,13 +158,9 @@ __device__ __forceinline__ void load_row(rsrc_t row, const Lane<kF32> &L, unsign
 #pragma unroll
     for (int l = 0; l < 9; ++l) {
       const int seg = seg_offset<kF32>(l);
-      if (L.vec) {
-        out[l] = __builtin_bit_cast(unsigned long long, __builtin_amdgcn_raw_buffer_load_b64(row, L.oe[0] + seg, 0, kLoadPolicy));
-      } else {
-        const u32x2 w = {__builtin_amdgcn_raw_buffer_load_b32(row, L.oe[0] + seg, 0, kLoadPolicy),
-                         __builtin_amdgcn_raw_buffer_load_b32(row, L.oe[1] + seg, 0, kLoadPolicy)};
-        out[l] = __builtin_bit_cast(unsigned long long, w);
-      }
+      const u32x2 w = {__builtin_amdgcn_raw_buffer_load_b32(row, L.oe[0] + seg, 0, kLoadPolicy),
+                       __builtin_amdgcn_raw_buffer_load_b32(row, L.oe[1] + seg, 0, kLoadPolicy)};
+      out[l] = __builtin_bit_cast(unsigned long long, w);
     }
   }
 }
@@ -205,7 +204,7 @@ using KapBuf = std::conditional_t<KF == kGammaKappa, u32x4v,
 template <int P, int KF> __device__ __forceinline__ void load_kappa(rsrc_t krow, const Lane<P> &L, KapBuf<P, KF> &out) {
   if constexpr (KF == kGammaKappa) {
     if constexpr (Form<P>::V == 2) {
-      if (L.allvecp || L.vecp) {
+      if (L.allvecp || (P == kF16S && L.vecp)) {
         out = __builtin_bit_cast(u32x4v, __builtin_amdgcn_raw_buffer_load_b128(krow, L.col[0] * 8, 0, kLoadPolicy));
       } else {
         const u32x2 w0 = __builtin_amdgcn_raw_buffer_load_b64(krow, L.col[0] * 8, 0, kLoadPolicy);
@@ -216,7 +215,7 @@ template <int P, int KF> __device__ __forceinline__ void load_kappa(rsrc_t krow,
       out = __builtin_bit_cast(u32x4v, __builtin_amdgcn_raw_buffer_load_b128(krow, L.col[0] * 16, 0, kLoadPolicy));
     }
   } else if constexpr (Form<P>::V == 2) {
-    if (L.allvecp || L.vecp) {
+    if (L.allvecp || (P == kF16S && L.vecp)) {
       out = __builtin_bit_cast(unsigned long long, __builtin_amdgcn_raw_buffer_load_b64(krow, L.col[0] * 4, 0, kLoadPolicy));
     } else {
       const u32x2 w = {__builtin_amdgcn_raw_buffer_load_b32(krow, L.col[0] * 4, 0, kLoadPolicy),
@@ -738,20 +737,10 @@ __device__ __forceinline__ void store_row(const StepArgs &A, int y, const typena
     }
   } else {
 #pragma unroll
-    for (int l = 0; l < 9; ++l) {
-      const rsrc_t rd = rowD[kCy[l] + 1];
-      const int seg = seg_offset<P>(l);
-      if constexpr (P == kF64) {
-        if (L.out[0]) st_f64(rd, L.oe[0] + seg, post[l][0]);
-      } else {
-        if (pair) {
-          st_f32x2(rd, L.oe[0] + seg, post[l][0], post[l][1]);
-        } else {
+    for (int v = 0; v < V; ++v) {
+      const int oe = L.out[v] ? L.oe[v] : kStoreDrop;
 #pragma unroll
-          for (int v = 0; v < V; ++v)
-            if (L.out[v]) st_f32(rd, L.oe[v] + seg, post[l][v]);
-        }
-      }
+      for (int l = 0; l < 9; ++l) st_t(rowD[kCy[l] + 1], oe + seg_offset<P>(l), post[l][v]);
     }
   }
   // zero the padding after each c_ly group of a full record so that its

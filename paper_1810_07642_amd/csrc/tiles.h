@@ -19,14 +19,15 @@ __host__ __device__ __forceinline__ bool block_active(int r0, int n, int rows, i
 }
 
 // Tiles of a pass of ns steps: 64 columns and r nw rows less three of each per
-// step and side.
+// step and side, and `extra` columns per side.
 struct Tiles {
-  int halo, bw, bh, ntx, ntiles, per_xcd;
+  int halo, halo_x, bw, bh, ntx, ntiles, per_xcd;
   unsigned inv_ntx;  // 2^32 / ntx rounded down, at most 2^32 - 1
   bool fits;         // the tile has an output worth launching for
-  Tiles(int nx, int ny, const BlockShape &sh, int ns) {
+  Tiles(int nx, int ny, const BlockShape &sh, int ns, int extra = 0) {
     halo = 3 * ns;
-    bw = 64 - 2 * halo;
+    halo_x = halo + extra;
+    bw = 64 - 2 * halo_x;
     bh = sh.r * sh.nw - 2 * halo;
     fits = bw >= 8 && bh >= 2;
     if (!fits) return;
@@ -68,7 +69,7 @@ struct BlockPlan {
 // (those without `pairs` left out if `pairs` asks for it), and that time;
 // TFLBM_<name> and TFLBM_<name>_SHAPE (`env`, `env_shape`) force both.
 // best.ns = 0 where no shape serves or TFLBM_<name>=0.
-double best_plan(const TileModel &m, const BlockShape *shapes, int n, int nx, int ny, bool pairs, const char *env,
-                 const char *env_shape, BlockPlan &best, bool &forced);
+double best_plan(const TileModel &m, const BlockShape *shapes, int n, int nx, int ny, int extra, bool pairs,
+                 const char *env, const char *env_shape, BlockPlan &best, bool &forced);
 
 }  // namespace tflbm

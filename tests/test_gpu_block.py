@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 # inside a tile), ragged ones, and whole multiples of no tile
 LATTICES = [(1, 1), (5, 3), (23, 37), (130, 97), (6, 300), (300, 6), (70, 150)]
 # rows of a tile per shape (rows per wavefront x wavefronts)
-SHAPES = {("fp32", 1.0): (32, 48, 80), ("fp32", 0.9): (32, 24), ("fp64", 1.0): (32, 36, 48), ("fp64", 0.9): (16, 24)}
+SHAPES = {("fp32", 1.0): (32, 48, 80), ("fp32", 0.9): (32, 24), ("fp16s", 1.0): (32, 48, 80), ("fp16s", 0.9): (32, 24),
+           ("fp64", 1.0): (32, 36, 48), ("fp64", 0.9): (16, 24)}
 CASES = [(prec, tau, shape) for (prec, tau), rows in SHAPES.items() for shape in range(len(rows))]
 
 
