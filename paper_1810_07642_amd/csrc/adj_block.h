@@ -24,13 +24,13 @@ namespace tflbm {
 // Shapes per working type and stage (BlockShapes of block.h; FP64 holds its
 // tile's adjoint, mu and the forward moments of two rows per wavefront at most).
 template <typename T, bool W1> struct AdjBlockShapes {
-  static constexpr BlockShape list[] = {{1, 12, true}, {2, 8, true}};
+  static constexpr BlockShape list[] = {{1, 12}, {2, 8}};
 };
 template <> struct AdjBlockShapes<float, true> {
-  static constexpr BlockShape list[] = {{2, 16, true}, {3, 12, true}};
+  static constexpr BlockShape list[] = {{2, 16}, {3, 12}};
 };
 template <> struct AdjBlockShapes<float, false> {
-  static constexpr BlockShape list[] = {{1, 16, true}, {2, 16, true}};
+  static constexpr BlockShape list[] = {{1, 16}, {2, 16}};
 };
 
 struct AdjBlockArgs {

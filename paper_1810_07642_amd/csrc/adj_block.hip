@@ -34,7 +34,7 @@ bool plan_adj_block(const tflbm_sim *s, BlockPlan &best) {
     return false;
   const TileModel &m = kModel[p.prec == kF64 ? 0 : 1][s->w1 ? 1 : 0];
   bool forced = false;
-  const double t = best_plan(m, shapes_of(p.prec, s->w1), 2, p.nx, p.ny, 0, false, "TFLBM_ADJ_BLOCK",
+  const double t = best_plan(m, shapes_of(p.prec, s->w1), 2, p.nx, p.ny, 0, "TFLBM_ADJ_BLOCK",
                              "TFLBM_ADJ_BLOCK_SHAPE", best, forced);
   if (best.ns == 0) return false;
   if (forced) return true;

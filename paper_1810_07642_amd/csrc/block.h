@@ -36,32 +36,33 @@
 
 namespace tflbm {
 
-// Shapes per storage form and stage: rows per wavefront, wavefronts per
-// workgroup, and whether the shape also takes a surface tension field (its
-// second value per site would spill FP64 rows of four).  A tile's cost is its
-// region, rows x 64, against the output that remains inside the halo, so a
-// lattice that leaves CUs idle wants low tiles and many steps, a larger one high
-// tiles; sixteen wavefronts (four per SIMD) issue FP32 twice as fast as two per
-// SIMD (2.1-2.6 against 4.2 cycles per instruction).  The lists hold the fewest
-// shapes within 1-7 % of the best of 14 (FP32, omega = 1), 9 and 4 measured.
+// Shapes per storage form and stage: rows per wavefront and wavefronts per
+// workgroup.  A tile's cost is its region, rows x 64, against the output that
+// remains inside the halo, so a lattice that leaves CUs idle wants low tiles and
+// many steps, a larger one high tiles; sixteen wavefronts (four per SIMD) issue
+// FP32 twice as fast as two per SIMD (2.1-2.6 against 4.2 cycles per
+// instruction), and FP64 a little faster than twelve (us per step at omega = 1,
+// tiles of 48 rows as 3 x 16 / 4 x 12: 512^2 5.2 / 5.3, 901x641 10.1 / 10.5).  The
+// lists hold the fewest shapes within 1-7 % of the best of 14 (FP32, omega = 1),
+// 9 and 4 measured.
 template <int P, bool W1> struct BlockShapes;
 template <> struct BlockShapes<kF32, true> {
-  static constexpr BlockShape list[] = {{2, 16, true}, {3, 16, true}, {5, 16, true}};
+  static constexpr BlockShape list[] = {{2, 16}, {3, 16}, {5, 16}};
 };
 template <> struct BlockShapes<kF32, false> {
-  static constexpr BlockShape list[] = {{2, 16, true}, {3, 8, true}};
+  static constexpr BlockShape list[] = {{2, 16}, {3, 8}};
 };
 template <> struct BlockShapes<kF16S, true> {
-  static constexpr BlockShape list[] = {{2, 16, true}, {3, 16, true}, {5, 16, true}};
+  static constexpr BlockShape list[] = {{2, 16}, {3, 16}, {5, 16}};
 };
 template <> struct BlockShapes<kF16S, false> {
-  static constexpr BlockShape list[] = {{2, 16, true}, {3, 8, true}};
+  static constexpr BlockShape list[] = {{2, 16}, {3, 8}};
 };
 template <> struct BlockShapes<kF64, true> {
-  static constexpr BlockShape list[] = {{2, 16, true}, {3, 12, true}, {4, 12, false}};
+  static constexpr BlockShape list[] = {{2, 16}, {3, 16}};
 };
 template <> struct BlockShapes<kF64, false> {
-  static constexpr BlockShape list[] = {{1, 16, true}, {2, 12, true}};
+  static constexpr BlockShape list[] = {{1, 16}, {2, 12}};
 };
 
 template <int P, bool W1, bool GF, bool G0, bool CAP, int R, int NW>

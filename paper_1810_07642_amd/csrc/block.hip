@@ -16,7 +16,7 @@ extern template hipError_t launch_block_form<kF32, true>(int, const BlockArgs &,
 extern template hipError_t launch_block_form<kF16S, false>(int, const BlockArgs &, hipStream_t);
 extern template hipError_t launch_block_form<kF16S, true>(int, const BlockArgs &, hipStream_t);
 
-double best_plan(const TileModel &m, const BlockShape *shapes, int n, int nx, int ny, int extra, bool pairs,
+double best_plan(const TileModel &m, const BlockShape *shapes, int n, int nx, int ny, int extra,
                  const char *env, const char *env_shape, BlockPlan &best, bool &forced) {
   best = BlockPlan();
   forced = false;
@@ -30,7 +30,7 @@ double best_plan(const TileModel &m, const BlockShape *shapes, int n, int nx, in
   if (const char *e = std::getenv(env_shape)) only = std::atoi(e);
   double best_t = 1e30;
   for (int i = 0; i < n; ++i) {
-    if ((only >= 0 && i != only) || (pairs && !shapes[i].pairs)) continue;
+    if (only >= 0 && i != only) continue;
     for (int ns = ns_min; ns <= ns_max; ++ns) {
       const Tiles t(nx, ny, shapes[i], ns, extra);
       if (!t.fits) break;
@@ -91,8 +91,7 @@ bool plan_block(const tflbm_sim *s, BlockPlan &best) {
   int n = 0;
   const BlockShape *shapes = shapes_of(p.prec, s->w1, n);
   bool forced = false;
-  const double t = best_plan(m, shapes, n, p.nx, p.ny, extra_columns(p.prec), s->kfield == kGammaKappa, "TFLBM_BLOCK",
-                             "TFLBM_BLOCK_SHAPE", best, forced);
+  const double t = best_plan(m, shapes, n, p.nx, p.ny, extra_columns(p.prec), "TFLBM_BLOCK", "TFLBM_BLOCK_SHAPE", best, forced);
   if (best.ns == 0) return false;
   if (forced) return true;
   const bool odd = p.prec == kF16S && (p.nx & 1) != 0;

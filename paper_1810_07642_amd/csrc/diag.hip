@@ -48,6 +48,10 @@ template <int P, int KF>
 __global__ __launch_bounds__(256) void terms_kernel(StepArgs A, double *partial) {
   __shared__ double sh[kDH][kDH], sjx[kDH][kDH], sjy[kDH][kDH];
   __shared__ double sp[kDP][kDP], sdv[kDP][kDP];
+  // u, formed once per site where nine neighbours divided for it: the kernel is
+  // bound by FP64 issue, most of it these divisions (4096^2 FP32 populations 628
+  // -> 534 us, FP16S 835 -> 742; FP64 718 -> 717, bound by its reads as well)
+  __shared__ double svx[kDP][kDP], svy[kDP][kDP];
   const int tid = threadIdx.y * kDT + threadIdx.x;
   const int nx = A.nx, ny = A.ny;
   const int tx = (nx + kDT - 1) / kDT, ty = (ny + kDT - 1) / kDT;
@@ -60,9 +64,10 @@ __global__ __launch_bounds__(256) void terms_kernel(StepArgs A, double *partial)
     for (int idx = tid; idx < kDH * kDH; idx += 256) {
       const int i = idx / kDH, j = idx % kDH;
       const int y = wrap(y0 - 2 + i, ny), x = wrap(x0 - 2 + j, nx);
+      const int xm = x == 0 ? nx - 1 : x - 1, xp = x + 1 == nx ? 0 : x + 1;
       double d[9];
 #pragma unroll
-      for (int l = 0; l < 9; ++l) d[l] = (double)pop_at<P>(A.src, l, y, wrap(x - kCx[l], nx), A);
+      for (int l = 0; l < 9; ++l) d[l] = (double)pop_at<P>(A.src, l, y, kCx[l] == 0 ? x : (kCx[l] > 0 ? xm : xp), A);
       double dh = d[0];
 #pragma unroll
       for (int l = 1; l < 9; ++l) dh += d[l];
@@ -90,6 +95,8 @@ __global__ __launch_bounds__(256) void terms_kernel(StepArgs A, double *partial)
         sp[i - 1][j - 1] = -A.gamma * (lap_s(sh, i, j) + kap * phi);
       }
       sdv[i - 1][j - 1] = dx_s(sjx, i, j) + dy_s(sjy, i, j);
+      svx[i - 1][j - 1] = sjx[i][j] / sh[i][j];
+      svy[i - 1][j - 1] = sjy[i][j] / sh[i][j];
     }
     __syncthreads();
     {
@@ -98,7 +105,7 @@ __global__ __launch_bounds__(256) void terms_kernel(StepArgs A, double *partial)
         const int I = i + 2, J = j + 2;  // in the h, j arrays
         const int Ip = i + 1, Jp = j + 1;  // in the p, div arrays
         const double h = sh[I][J];
-        const double ux = sjx[I][J] / h, uy = sjy[I][J] / h;
+        const double ux = svx[Ip][Jp], uy = svy[Ip][Jp];
         const double alpha = 6.0 * h / (2.0 * h * h + 6.0 * A.delta * h + 3.0 * A.delta * A.delta);
         double t[8];
         t[0] = -h * dx_s(sp, Ip, Jp);
@@ -113,8 +120,8 @@ __global__ __launch_bounds__(256) void terms_kernel(StepArgs A, double *partial)
         for (int a = -1; a <= 1; ++a)
 #pragma unroll
           for (int b = -1; b <= 1; ++b) {
-            const double hh = sh[I + a][J + b], jx = sjx[I + a][J + b], jy = sjy[I + a][J + b];
-            const double vx = jx / hh, vy = jy / hh;
+            const double jx = sjx[I + a][J + b], jy = sjy[I + a][J + b];
+            const double vx = svx[Ip + a][Jp + b], vy = svy[Ip + a][Jp + b];
             q[a + 1][b + 1][0] = jx * vx;
             q[a + 1][b + 1][1] = jy * vx;
             q[a + 1][b + 1][2] = jx * vy;

@@ -8,8 +8,7 @@
 namespace tflbm {
 
 struct BlockShape {
-  int r, nw;   // rows per wavefront, wavefronts per workgroup
-  bool pairs;  // the shape takes a surface tension field (forward kernel)
+  int r, nw;  // rows per wavefront, wavefronts per workgroup
 };
 
 // Whether the n tile rows from r0 on, of `rows` in use, hold a row whose
@@ -65,11 +64,10 @@ struct BlockPlan {
   int shape = 0, ns = 0;
 };
 
-// The shape and steps per pass of the least modelled time per step, of n shapes
-// (those without `pairs` left out if `pairs` asks for it), and that time;
-// TFLBM_<name> and TFLBM_<name>_SHAPE (`env`, `env_shape`) force both.
+// The shape and steps per pass of the least modelled time per step, of n shapes,
+// and that time; TFLBM_<name> and TFLBM_<name>_SHAPE (`env`, `env_shape`) force both.
 // best.ns = 0 where no shape serves or TFLBM_<name>=0.
-double best_plan(const TileModel &m, const BlockShape *shapes, int n, int nx, int ny, int extra, bool pairs,
+double best_plan(const TileModel &m, const BlockShape *shapes, int n, int nx, int ny, int extra,
                  const char *env, const char *env_shape, BlockPlan &best, bool &forced);
 
 }  // namespace tflbm
