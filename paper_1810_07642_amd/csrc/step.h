@@ -930,7 +930,11 @@ template <typename T, int V> struct Handoff {
 // pre-collision state on the tile's own rows go to the capture: step t at
 // A.capture, step t + s s capture blocks later.
 // G0 (FP16S only): the launch has g = 0, so the rest equilibrium of the
-// FP16S shift has no moving part and its code is left out.
+// FP16S shift has no moving part and its code and the hydrostatic part of the
+// collision are left out, and the two-step kernels keep 1/h (Stage's RH): a call
+// of 100 steps at 2048^2 3300 -> 3246 us, 4096^2 unchanged (98 us per step).  FP32
+// and FP64 with the same gained nothing (tau = 0.9 at 4096 x 2048, us per step: FP64
+// 145.6 / 145.1, FP32 83.4 / 82.5), and 1/h kept with g != 0 lost 2 % (67.0 / 68.4).
 // W1: omega = 1, the stages keep no populations (Stage), only j of two rows
 // in LDS, which lets three fused steps keep eight wavefronts per CU.
 template <int P, int KF, bool CAP, int NS, bool G0 = false, bool W1 = false>
@@ -964,7 +968,8 @@ __global__ __launch_bounds__(64, 2) void step_kernel(StepArgs A) {
   const Lane<P> L(x0 - HX + V * lane, x0, xend, A.nx);
   const Coef<T> C(A);
 
-  Stage<P, KF, W1> S0, S1, S2;
+  constexpr bool RH = G0 && NS >= 2 && KF != kGammaKappa;
+  Stage<P, KF, W1, G0, RH> S0, S1, S2;
   if constexpr (W1) {
     S0.jhist = jhist[0];
     if constexpr (NS >= 2) S1.jhist = jhist[1];
