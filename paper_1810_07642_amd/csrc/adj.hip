@@ -780,12 +780,16 @@ int tflbm_adj_steps(tflbm_sim *sim, void *d_adj, const void *d_capture, int64_t 
   const size_t cb = tflbm_capture_bytes(sim);
   const char *cap = (const char *)d_capture;
   const bool fuse = sim->adj_fuse == 2 || (sim->adj_fuse == 0 && sim->adj_fuse_fits);
-  if (sim->adj_block.ns > 0 && nsteps > 0) {
-    // passes of nearly equal length, their number even or odd with that of the
-    // marching passes, so that a caller's own graph of them ends, as before, on
-    // the buffer it started from
-    int64_t k = (nsteps + sim->adj_block.ns - 1) / sim->adj_block.ns;
+  // block passes of nearly equal length, their number even or odd with that of
+  // the marching passes, so that a caller's own graph of them ends, as before, on
+  // the buffer it started from; the marching kernel where that makes every pass a
+  // single step (launch_steps)
+  int64_t k = 0;
+  if (sim->adj_block.ns > 0) {
+    k = (nsteps + sim->adj_block.ns - 1) / sim->adj_block.ns;
     if (k < nsteps) k += (k ^ (fuse ? (nsteps + 1) / 2 : nsteps)) & 1;
+  }
+  if (k > 0 && (k < nsteps || sim->adj_block.always)) {
     int64_t left = nsteps;
     for (; k > 0; --k) {
       const int ns = (int)((left + k - 1) / k);

@@ -32,13 +32,13 @@ bool plan_adj_block(const tflbm_sim *s, BlockPlan &best) {
   const size_t row = (size_t)s->adj_nstrips * adj_record_bytes_max(p.prec);
   if (row * p.ny >= (size_t)kDropBytes || s->kf_bytes >= (size_t)kDropBytes || tflbm_capture_bytes(s) >= (size_t)kDropBytes)
     return false;
+  if ((int64_t)p.nx * p.ny > kAdjBlockMaxSites && std::getenv("TFLBM_ADJ_BLOCK") == nullptr) return false;
   const TileModel &m = kModel[p.prec == kF64 ? 0 : 1][s->w1 ? 1 : 0];
-  bool forced = false;
   const double t = best_plan(m, shapes_of(p.prec, s->w1), 2, p.nx, p.ny, 0, "TFLBM_ADJ_BLOCK",
-                             "TFLBM_ADJ_BLOCK_SHAPE", best, forced);
+                             "TFLBM_ADJ_BLOCK_SHAPE", best);
   if (best.ns == 0) return false;
-  if (forced) return true;
-  return (int64_t)p.nx * p.ny <= kAdjBlockMaxSites && t < 0.9 * m.march((double)s->adj_nstrips * p.ny, m.march2);
+  if (best.always) return true;
+  return best.ns >= 2 && t < 0.9 * m.march((double)s->adj_nstrips * p.ny, m.march2);
 }
 
 hipError_t launch_adj_block(const tflbm_sim *s, const AdjArgs &B, int64_t cap_stride, int ns, hipStream_t st) {

@@ -159,11 +159,12 @@ void plan_launches(tflbm_sim *s) {
   // pass (4096^2: 188.8 vs 284.8 us).
   s->adj_fuse_fits = !(s->w1 && s->p.prec == kF64) &&
                      (int64_t)s->adj_nstrips * ((ny + kMinRowsAdj2 - 1) / kMinRowsAdj2) > (int64_t)aocc2 * cus;
-  plan_march(s, cus);
+  plan_march(s);
   // the block kernel, unless a variable asks for a shape of the marching one
   bool march = s->fuse != 0;
   for (const char *v : {"TFLBM_ROWS", "TFLBM_ROWS2", "TFLBM_ROWS3"}) march = march || std::getenv(v) != nullptr;
   if (march || !plan_block(s, s->block)) s->block = BlockPlan();
+  if (s->block.ns == 0) shape_march(s, cus);  // (the block plan's calls of up to three steps hand over no moments)
   // the reverse block kernel, likewise
   march = s->adj_fuse != 0;
   for (const char *v : {"TFLBM_ADJ_ROWS", "TFLBM_ADJ_ROWS2"}) march = march || std::getenv(v) != nullptr;
@@ -387,10 +388,14 @@ static int march_steps_per_pass(const tflbm_sim *sim) {
 // made even or odd with that of the marching kernel's passes, so that a
 // caller's own graph of these steps ends, as before, on the buffer it started
 // from.
-static int launch_block_steps(tflbm_sim *sim, int64_t nsteps, void *d_capture, hipStream_t st) {
+static int64_t block_passes(const tflbm_sim *sim, int64_t nsteps) {
   const int ns_march = march_steps_per_pass(sim);
   int64_t k = (nsteps + sim->block.ns - 1) / sim->block.ns;
   if (k < nsteps) k += (k ^ ((nsteps + ns_march - 1) / ns_march)) & 1;
+  return k;
+}
+
+static int launch_block_steps(tflbm_sim *sim, int64_t nsteps, int64_t k, void *d_capture, hipStream_t st) {
   const size_t cap_bytes = tflbm_capture_bytes(sim);
   int64_t done = 0;
   for (int64_t i = 0; i < k; ++i) {
@@ -439,7 +444,13 @@ static int launch_march_steps(tflbm_sim *sim, const MarchSplit &sp, void *d_capt
 // handle allows while that many remain, then shorter ones (with capture: the
 // moments of steps i .. i + ns - 1 of a pass, one capture block apart).
 static int launch_steps(tflbm_sim *sim, int64_t nsteps, void *d_capture, hipStream_t st) {
-  if (sim->block.ns > 0) return launch_block_steps(sim, nsteps, d_capture, st);
+  if (sim->block.ns > 0) {
+    // A call whose passes would all be single steps (one step, or two or three
+    // made so by the rule above) goes to the marching kernel, whose step costs less
+    // than a tile's load and store: FP64 64^2 4.5 us against 6.3 in a pass of one.
+    const int64_t k = block_passes(sim, nsteps);
+    if (k < nsteps || sim->block.always) return launch_block_steps(sim, nsteps, k, d_capture, st);
+  }
   const size_t cap_bytes = tflbm_capture_bytes(sim);
   const int ns_max = march_steps_per_pass(sim);
   MarchSplit sp;

@@ -17,15 +17,14 @@ extern template hipError_t launch_block_form<kF16S, false>(int, const BlockArgs 
 extern template hipError_t launch_block_form<kF16S, true>(int, const BlockArgs &, hipStream_t);
 
 double best_plan(const TileModel &m, const BlockShape *shapes, int n, int nx, int ny, int extra,
-                 const char *env, const char *env_shape, BlockPlan &best, bool &forced) {
+                 const char *env, const char *env_shape, BlockPlan &best) {
   best = BlockPlan();
-  forced = false;
   int ns_min = 1, ns_max = 9, only = -1;
   if (const char *e = std::getenv(env)) {
     const int v = std::atoi(e);
     if (v <= 0) return 0.0;
     ns_min = ns_max = v;
-    forced = true;
+    best.always = true;
   }
   if (const char *e = std::getenv(env_shape)) only = std::atoi(e);
   double best_t = 1e30;
@@ -77,7 +76,8 @@ static const BlockShape *shapes_of(int prec, bool w1, int &n) {
 static int extra_columns(int prec) { return prec == kF16S ? 1 : 0; }
 
 // False where the marching kernels are faster, or the block kernel does not
-// serve the handle: disjoining exponents other than (9, 3) and (3, 9), arrays its 32-bit row offsets do not reach.
+// serve the handle: disjoining exponents other than (9, 3) and (3, 9), arrays its
+// 32-bit row offsets do not reach.
 bool plan_block(const tflbm_sim *s, BlockPlan &best) {
   best = BlockPlan();
   const tflbm_params &p = s->p;
@@ -88,16 +88,20 @@ bool plan_block(const tflbm_sim *s, BlockPlan &best) {
     return false;
   const int f = p.prec == kF64 ? 0 : (p.prec == kF32 ? 1 : 2);
   const TileModel &m = kModel[f][s->w1 ? 1 : 0];
+  const bool odd = p.prec == kF16S && (p.nx & 1) != 0;
+  if (!odd && (int64_t)p.nx * p.ny > kBlockMaxSites && std::getenv("TFLBM_BLOCK") == nullptr) return false;
   int n = 0;
   const BlockShape *shapes = shapes_of(p.prec, s->w1, n);
-  bool forced = false;
-  const double t = best_plan(m, shapes, n, p.nx, p.ny, extra_columns(p.prec), "TFLBM_BLOCK", "TFLBM_BLOCK_SHAPE", best, forced);
+  const double t = best_plan(m, shapes, n, p.nx, p.ny, extra_columns(p.prec), "TFLBM_BLOCK", "TFLBM_BLOCK_SHAPE", best);
   if (best.ns == 0) return false;
-  if (forced) return true;
-  const bool odd = p.prec == kF16S && (p.nx & 1) != 0;
-  if (!odd && (int64_t)p.nx * p.ny > kBlockMaxSites) return false;
+  if (best.always) return true;
+  if (best.ns < 2 && !odd) return false;  // as many launches as the marching kernel's
   // (a tie stays with the marching kernels)
   const double march = m.march((double)s->nstrips * p.ny, s->march_ns > 0 ? kMarchMoments[f] : m.march2);
+  if (odd) {
+    const Tiles one(p.nx, p.ny, shapes[best.shape], 1, extra_columns(p.prec));
+    best.always = m.pass(one, shapes[best.shape], 1) < kOddF16 * march;
+  }
   // and so does a surface tension field where that is near (FP32, general stages,
   // 808x1306: 25 us per step against 16)
   return t < (s->kfield == kGammaKappa ? 0.75 : 0.9) * march * (odd ? kOddF16 : 1.0);

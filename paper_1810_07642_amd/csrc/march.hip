@@ -33,11 +33,15 @@ static int strip_columns(int prec, int kind) {
 // FP64 1536^2 26.4 / 26.9, 2048^2 35.7 / 39.4, 4096^2 149.4 / 132.5.
 constexpr int64_t kMarch3MinSites = 8000000;
 
-void plan_march(tflbm_sim *s, int cus) {
+void plan_march(tflbm_sim *s) {
   s->march_ns = 0;
   if (!s->w1 || s->p.prec == kF16S || s->kfield == kGammaKappa || s->fuse != 0) return;
   s->march_ns = (int64_t)s->p.nx * s->p.ny >= kMarch3MinSites ? 3 : 2;
   if (const char *e = std::getenv("TFLBM_MARCH")) s->march_ns = std::atoi(e) <= 0 ? 0 : (std::atoi(e) >= 3 ? 3 : 2);
+}
+
+// Launch shapes of the passes.
+void shape_march(tflbm_sim *s, int cus) {
   if (s->march_ns == 0) return;
   const StepArgs A = make_step_args(s);
   for (int kind = 0; kind < kMarchKinds; ++kind) {

@@ -87,7 +87,8 @@ bool plan_adj_block(const tflbm_sim *s, BlockPlan &best);
 struct MarchSplit {
   int64_t passes, threes;
 };
-void plan_march(tflbm_sim *s, int cus);
+void plan_march(tflbm_sim *s);
+void shape_march(tflbm_sim *s, int cus);
 bool split_march(int64_t nsteps, int64_t passes_before, int ns, MarchSplit &sp);
 
 // Releases the captured step graphs of `s`, after waiting for the device.

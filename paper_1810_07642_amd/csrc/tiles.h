@@ -49,9 +49,7 @@ struct TileModel {
   double launch, step, row_load, row_step, step_load, whole, march0, march1, march2;
   double pass(const Tiles &t, const BlockShape &sh, int ns) const {
     int row_steps = 0;
-    for (int k = 0; k < ns; ++k)
-      for (int w = 0; w < sh.nw; ++w)
-        if (block_active(w * sh.r, sh.r, sh.r * sh.nw, k)) row_steps += sh.r;
+    for (int k = 0; k < ns; ++k) row_steps += sh.r * (sh.nw - 2 * ((3 * k + 1) / sh.r));  // wavefronts with block_active
     const double per_cu = t.ntiles / 256.0, up = (double)(int64_t)(per_cu + 0.999999);
     const double load = per_cu <= 1.0 ? 1.0 : per_cu + whole * (up - per_cu);
     return launch + step * ns + load * (row_load * sh.r * sh.nw + row_step * row_steps + step_load * ns);
@@ -62,12 +60,13 @@ struct TileModel {
 // A block plan: index of the shape and most steps per pass (0: no plan).
 struct BlockPlan {
   int shape = 0, ns = 0;
+  bool always = false;  // also for calls whose passes are single steps
 };
 
 // The shape and steps per pass of the least modelled time per step, of n shapes,
 // and that time; TFLBM_<name> and TFLBM_<name>_SHAPE (`env`, `env_shape`) force both.
 // best.ns = 0 where no shape serves or TFLBM_<name>=0.
 double best_plan(const TileModel &m, const BlockShape *shapes, int n, int nx, int ny, int extra,
-                 const char *env, const char *env_shape, BlockPlan &best, bool &forced);
+                 const char *env, const char *env_shape, BlockPlan &best);
 
 }  // namespace tflbm

@@ -79,3 +79,17 @@ def test_block_kernel_flags_bad_heights():
                 assert sim.status() == TFLBM_ENONFINITE, (bad, at)
     finally:
         del os.environ["TFLBM_BLOCK"]
+
+
+@pytest.mark.parametrize("prec,tau", list(SHAPES))
+def test_short_calls_equal_marching_kernel_bitwise(prec, tau):
+    """Calls of a few steps, which the default plan gives to one kernel or the
+    other, in a row on one handle."""
+    for (ny, nx) in ((67, 90), (137, 553), (256, 256), (320, 704), (151, 1001)):
+        p = dict(tau=tau, gamma=0.01, g=0.0, hstar=0.1, delta=1.0, ax=1e-5, ay=-1e-5, n=9, m=3, href=0.4)
+        for steps in (1, 2, 3, 4):
+            banner(f"short calls: {prec} tau={tau} {ny}x{nx} {steps} steps")
+            ref, _ = run(prec, ny, nx, "theta", steps, {"TFLBM_BLOCK": "0"}, p)
+            got, _ = run(prec, ny, nx, "theta", steps, {}, p)
+            for a, b in zip(got, ref):
+                assert torch.equal(a, b), (ny, nx, steps)
