@@ -4,11 +4,12 @@
 //
 // A workgroup of NW wavefronts owns a tile of 64 columns and NW R rows: lane i
 // of wavefront w holds column i of the rows w R .. w R + R - 1.  The outermost
-// `halo` = 3 ns columns and rows of the tile are re-computed by its neighbours (a
-// step reads three sites in each direction); the rest is stored after ns steps.  Stencil neighbours in x come from
-// adjacent lanes, in y from the lane's own registers and, at the edge of a
-// wavefront's rows, from the neighbouring wavefront through LDS: dh, then the
-// film pressure, then the six populations that stream across, a barrier each.
+// `halo` = 3 ns columns and rows of the tile are re-computed by its neighbours
+// (a step reads three sites in each direction); the rest is stored after ns
+// steps.  Stencil neighbours in x come from adjacent lanes, in y from the
+// lane's own registers and, at the edge of a wavefront's rows, from the
+// neighbouring wavefront through LDS: dh, then the film pressure, then the six
+// populations that stream across, a barrier each.
 //
 // With omega = 1 a site's populations are a function of its moments and force,
 // so nothing but dh and j has to leave the chip between two passes of a call:
