@@ -782,14 +782,14 @@ int tflbm_adj_steps(tflbm_sim *sim, void *d_adj, const void *d_capture, int64_t 
   const bool fuse = sim->adj_fuse == 2 || (sim->adj_fuse == 0 && sim->adj_fuse_fits);
   // block passes of nearly equal length, their number even or odd with that of
   // the marching passes, so that a caller's own graph of them ends, as before, on
-  // the buffer it started from; the marching kernel where that makes every pass a
-  // single step (launch_steps)
+  // the buffer it started from; the marching kernel where it is the faster one
+  // for these passes (adj_block_takes)
   int64_t k = 0;
   if (sim->adj_block.ns > 0) {
     k = (nsteps + sim->adj_block.ns - 1) / sim->adj_block.ns;
     if (k < nsteps) k += (k ^ (fuse ? (nsteps + 1) / 2 : nsteps)) & 1;
   }
-  if (k > 0 && (k < nsteps || sim->adj_block.always)) {
+  if (k > 0 && adj_block_takes(sim, nsteps, k)) {
     int64_t left = nsteps;
     for (; k > 0; --k) {
       const int ns = (int)((left + k - 1) / k);

@@ -79,6 +79,7 @@ bool plan_block(const tflbm_sim *s, BlockPlan &best);
 void shape_block(const tflbm_sim *s, int shape, int ns, BlockArgs &A);
 // The same for the reverse block kernel.
 bool plan_adj_block(const tflbm_sim *s, BlockPlan &best);
+bool adj_block_takes(const tflbm_sim *s, int64_t nsteps, int64_t k);
 
 // Passes that hand over moments: their plan, and the split of a call of nsteps
 // steps into `passes` passes, the first of two steps, `threes` of the others of

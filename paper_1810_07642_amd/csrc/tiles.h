@@ -54,6 +54,15 @@ struct TileModel {
     const double load = per_cu <= 1.0 ? 1.0 : per_cu + whole * (up - per_cu);
     return launch + step * ns + load * (row_load * sh.r * sh.nw + row_step * row_steps + step_load * ns);
   }
+  // k passes of nearly equal length over n steps, the longer ones first
+  double call(int nx, int ny, const BlockShape &sh, int extra, int64_t n, int64_t k) const {
+    const int q = (int)(n / k);
+    const int64_t longer = n % k;
+    const Tiles t(nx, ny, sh, q, extra);
+    double us = (double)(k - longer) * pass(t, sh, q);
+    if (longer > 0) us += (double)longer * pass(Tiles(nx, ny, sh, q + 1, extra), sh, q + 1);
+    return us;
+  }
   double march(double n, double slope) const { return march0 + march1 * (n < 2500 ? n : 2500) + slope * (n < 2500 ? 0 : n - 2500); }
 };
 
@@ -61,6 +70,7 @@ struct TileModel {
 struct BlockPlan {
   int shape = 0, ns = 0;
   bool always = false;  // also for calls whose passes are single steps
+  double limit = 0.0;   // modelled time per step from which on a call stays with the marching kernels
 };
 
 // The shape and steps per pass of the least modelled time per step, of n shapes,
