@@ -164,7 +164,7 @@ void plan_launches(tflbm_sim *s) {
   bool march = s->fuse != 0;
   for (const char *v : {"TFLBM_ROWS", "TFLBM_ROWS2", "TFLBM_ROWS3"}) march = march || std::getenv(v) != nullptr;
   if (march || !plan_block(s, s->block)) s->block = BlockPlan();
-  if (s->block.ns == 0) shape_march(s, cus);  // (the block plan's calls of up to three steps hand over no moments)
+  shape_march(s, cus);  // (also of a handle with a block plan, which does not take every call)
   // the reverse block kernel, likewise
   march = s->adj_fuse != 0;
   for (const char *v : {"TFLBM_ADJ_ROWS", "TFLBM_ADJ_ROWS2"}) march = march || std::getenv(v) != nullptr;
@@ -445,11 +445,8 @@ static int launch_march_steps(tflbm_sim *sim, const MarchSplit &sp, void *d_capt
 // moments of steps i .. i + ns - 1 of a pass, one capture block apart).
 static int launch_steps(tflbm_sim *sim, int64_t nsteps, void *d_capture, hipStream_t st) {
   if (sim->block.ns > 0) {
-    // A call whose passes would all be single steps (one step, or two or three
-    // made so by the rule above) goes to the marching kernel, whose step costs less
-    // than a tile's load and store: FP64 64^2 4.5 us against 6.3 in a pass of one.
     const int64_t k = block_passes(sim, nsteps);
-    if (k < nsteps || sim->block.always) return launch_block_steps(sim, nsteps, k, d_capture, st);
+    if (block_takes(sim, nsteps, k, d_capture != nullptr)) return launch_block_steps(sim, nsteps, k, d_capture, st);
   }
   const size_t cap_bytes = tflbm_capture_bytes(sim);
   const int ns_max = march_steps_per_pass(sim);

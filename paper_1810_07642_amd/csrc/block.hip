@@ -60,6 +60,25 @@ constexpr double kOddF16 = 2.3;
 constexpr double kMarchMoments[3] = {0.28e-3, 0.385e-3, 0};
 // Largest lattice the model was fitted to.
 constexpr int64_t kBlockMaxSites = 1500000;
+// A call is taken where the model puts its own passes below this fraction of the
+// marching kernels' time: [FP64, FP32, FP16S][stages][two steps or less, an odd number
+// below ten, others].  What the model leaves out sets the lines, and only where the
+// tiles take more than one round of the GPU, or at omega = 1 two steps write captures
+// (1 otherwise).  At omega = 1 a call's first
+// and last pass move populations (us per step, marching / block: FP32 1165x1007 2
+// steps 16.6 / 22.1, 4 steps 15.9 / 18.6, 24 steps 13.6 / 13.3; FP64 723x817 2 steps
+// 15.1 / 18.1, 24 steps 10.6 / 10.2), but the marching kernels have no passes that
+// suit short odd calls (FP64 658x740 3 steps with captures 18.6 / 15.2).  Captures go
+// out in parts of lines from tiles of 52 columns and less (FP32 general 1232x911
+// without 17.9 / 16.4, with 19.1 / 25.2; 1157x327 with 12.1 / 9.2).  The lines are drawn
+// from 2500 calls of 2 to 32 steps on 190 lattices where the model sees between 0.55 and
+// the whole of the marching time.
+enum CallKind { kGeneral = 0, kGeneralCap = 1, kOmega1 = 2, kOmega1Cap = 3 };
+constexpr double kLimit[3][4][3] = {{{1.00, 1.00, 1.00}, {0.90, 0.90, 0.90}, {0.76, 1.00, 0.86}, {0.60, 1.00, 0.86}},
+                                    {{0.95, 0.95, 0.95}, {0.69, 0.69, 0.69}, {0.70, 0.90, 0.80}, {0.56, 0.85, 0.73}},
+                                    {{1.00, 1.00, 1.00}, {0.90, 0.90, 0.90}, {0.84, 0.88, 0.86}, {0.68, 0.86, 0.86}}};
+// And a plan is made where some call of many steps takes it.
+constexpr double kPlanLimit[3][2] = {{0.90, 0.86}, {0.90, 0.80}, {0.90, 0.86}};  // [form][general, omega = 1]
 
 static const BlockShape *shapes_of(int prec, bool w1, int &n) {
   auto of = [&](const auto &list) {
@@ -75,6 +94,8 @@ static const BlockShape *shapes_of(int prec, bool w1, int &n) {
 // stored and shifts them into place.
 static int extra_columns(int prec) { return prec == kF16S ? 1 : 0; }
 
+static int form_of(int prec) { return prec == kF64 ? 0 : (prec == kF32 ? 1 : 2); }
+
 // False where the marching kernels are faster, or the block kernel does not
 // serve the handle: disjoining exponents other than (9, 3) and (3, 9), arrays its
 // 32-bit row offsets do not reach.
@@ -86,7 +107,7 @@ bool plan_block(const tflbm_sim *s, BlockPlan &best) {
   if (s->pop_bytes >= (size_t)kDropBytes || s->kf_bytes >= (size_t)kDropBytes ||
       tflbm_capture_bytes(s) >= (size_t)kDropBytes)
     return false;
-  const int f = p.prec == kF64 ? 0 : (p.prec == kF32 ? 1 : 2);
+  const int f = form_of(p.prec);
   const TileModel &m = kModel[f][s->w1 ? 1 : 0];
   const bool odd = p.prec == kF16S && (p.nx & 1) != 0;
   if (!odd && (int64_t)p.nx * p.ny > kBlockMaxSites && std::getenv("TFLBM_BLOCK") == nullptr) return false;
@@ -94,17 +115,36 @@ bool plan_block(const tflbm_sim *s, BlockPlan &best) {
   const BlockShape *shapes = shapes_of(p.prec, s->w1, n);
   const double t = best_plan(m, shapes, n, p.nx, p.ny, extra_columns(p.prec), "TFLBM_BLOCK", "TFLBM_BLOCK_SHAPE", best);
   if (best.ns == 0) return false;
-  if (best.always) return true;
-  if (best.ns < 2 && !odd) return false;  // as many launches as the marching kernel's
-  // (a tie stays with the marching kernels)
-  const double march = m.march((double)s->nstrips * p.ny, s->march_ns > 0 ? kMarchMoments[f] : m.march2);
-  if (odd) {
-    const Tiles one(p.nx, p.ny, shapes[best.shape], 1, extra_columns(p.prec));
-    best.always = m.pass(one, shapes[best.shape], 1) < kOddF16 * march;
+  if (best.always) {
+    best.limit = 1e30;
+    return true;
   }
-  // and so does a surface tension field where that is near (FP32, general stages,
-  // 808x1306: 25 us per step against 16)
-  return t < (s->kfield == kGammaKappa ? 0.75 : 0.9) * march * (odd ? kOddF16 : 1.0);
+  if (best.ns < 2 && !odd) return false;  // as many launches as the marching kernel's
+  // a surface tension field stays with the marching kernels where that is near (FP32,
+  // general stages, 808x1306: 25 us per step against 16)
+  const bool gamma = s->kfield == kGammaKappa;
+  best.limit = m.march((double)s->nstrips * p.ny, s->march_ns > 0 ? kMarchMoments[f] : m.march2) *
+               (odd ? kOddF16 : 1.0) * (gamma ? 0.75 / 0.9 : 1.0);
+  best.always = odd;
+  return t < kPlanLimit[f][s->w1 && !gamma ? 1 : 0] * best.limit;
+}
+
+// Whether a call of nsteps steps takes the plan, in k passes.  Not where all of them
+// are single steps, which the marching kernel does for less than a tile's load and
+// store (FP64 64^2 4.5 us against 6.3 in a pass of one), odd widths of FP16S excepted;
+// nor where they are modelled too slow.
+bool block_takes(const tflbm_sim *s, int64_t nsteps, int64_t k, bool capture) {
+  const BlockPlan &b = s->block;
+  if (b.ns == 0 || nsteps == 0 || (k >= nsteps && !b.always)) return false;
+  const tflbm_params &p = s->p;
+  const int f = form_of(p.prec), extra = extra_columns(p.prec);
+  int n = 0;
+  const BlockShape &sh = shapes_of(p.prec, s->w1, n)[b.shape];
+  const int kind = (s->w1 && s->kfield != kGammaKappa ? kOmega1 : kGeneral) + (capture ? 1 : 0);
+  const int length = nsteps <= 2 ? 0 : (nsteps < 10 && (nsteps & 1) ? 1 : 2);
+  const bool one_round = Tiles(p.nx, p.ny, sh, (int)((nsteps + k - 1) / k), extra).ntiles <= 256;
+  const double limit = one_round && !(kind == kOmega1Cap && length == 0) ? 1.0 : kLimit[f][kind][length];
+  return kModel[f][s->w1 ? 1 : 0].call(p.nx, p.ny, sh, extra, nsteps, k) < limit * b.limit * (double)nsteps;
 }
 
 // Launch shape of a pass of ns steps of a plan.

@@ -73,9 +73,11 @@ int choose_rows(int ny, int nstrips, int slots, int min_rows, const char *env_na
 // Chooses the launch shapes of the step kernels (needs the device).
 void plan_launches(tflbm_sim *s);
 
-// The block kernel's plan for the handle (false: the marching kernel is to run)
-// and its launch shape for a pass of ns steps.
+// The block kernel's plan for the handle (false: the marching kernel is to run),
+// whether a call of nsteps steps takes it, in k passes, and its launch shape for a
+// pass of ns steps.
 bool plan_block(const tflbm_sim *s, BlockPlan &best);
+bool block_takes(const tflbm_sim *s, int64_t nsteps, int64_t k, bool capture);
 void shape_block(const tflbm_sim *s, int shape, int ns, BlockArgs &A);
 // The same for the reverse block kernel.
 bool plan_adj_block(const tflbm_sim *s, BlockPlan &best);

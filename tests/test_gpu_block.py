@@ -93,3 +93,16 @@ def test_short_calls_equal_marching_kernel_bitwise(prec, tau):
             got, _ = run(prec, ny, nx, "theta", steps, {}, p)
             for a, b in zip(got, ref):
                 assert torch.equal(a, b), (ny, nx, steps)
+
+
+@pytest.mark.parametrize("prec,nx,ny", [("fp64", 480, 1301), ("fp32", 840, 1070)])
+def test_calls_that_leave_the_plan_equal_single_steps_bitwise(prec, nx, ny):
+    """Lattices whose calls go to the block kernel, the passes of moments or the
+    marching kernel by their length, in a row on one handle."""
+    p = dict(tau=1.0, gamma=0.01, g=0.0, hstar=0.1, delta=1.0, ax=1e-5, ay=-1e-5, n=9, m=3, href=0.4)
+    for steps in (4, 7, 24):
+        banner(f"calls that leave the plan: {prec} {ny}x{nx} {steps} steps")
+        ref, _ = run(prec, ny, nx, "theta", steps, {"TFLBM_FUSE": "1"}, p)
+        got, _ = run(prec, ny, nx, "theta", steps, {}, p)
+        for a, b in zip(got, ref):
+            assert torch.equal(a, b), steps

@@ -27,3 +27,34 @@ def kernels(exe, case, call):
 def test_reverse_calls_take_the_faster_kernel(exe, case, steps, block):
     names = kernels(exe, case, f"adj {steps}")
     assert all(("adj_block_kernel" in n) == block for n in names), names
+
+
+@pytest.mark.parametrize("case,call,block", [
+    # measured, us per step marching / block
+    (dict(nx=744, ny=922, prec="fp32"), "capture 2", False),              # 13.0 / 13.6
+    (dict(nx=744, ny=922, prec="fp32"), "step 24", True),                 # 10.6 / 6.8
+    (dict(nx=1165, ny=1007, prec="fp32"), "step 4", False),               # 15.9 / 18.6
+    (dict(nx=784, ny=597, prec="fp64"), "step 2", False),                 # 13.0 / 12.9
+    (dict(nx=784, ny=597, prec="fp64"), "step 7", True),                  # odd: 1 / 0.7
+    (dict(nx=723, ny=817, prec="fp64"), "step 4", False),                 # 13.3 / 15.2
+    (dict(nx=1232, ny=911, prec="fp32", tau=0.9), "capture 4", False),    # 19.1 / 25.0
+    (dict(nx=1232, ny=911, prec="fp32", tau=0.9), "step 4", True),        # 17.9 / 16.4
+    (dict(nx=1157, ny=327, prec="fp32", tau=0.9), "capture 4", True),     # 12.1 / 9.2
+    (dict(nx=568, ny=1446, prec="fp16s"), "capture 2", False),            # 13.3 / 14.0
+    (dict(nx=128, ny=128, prec="fp32"), "capture 3", True),
+    (dict(nx=128, ny=128, prec="fp32"), "step 2", False)])
+def test_forward_calls_take_the_faster_kernel(exe, case, call, block):
+    names = kernels(exe, case, call)
+    assert all(("12block_kernel" in n) == block for n in names), names
+
+
+def test_calls_that_leave_a_block_plan_launch_whole_grids(exe):
+    """Passes of moments on a handle with a block plan, which serves its longer calls."""
+    seen = 0
+    for case in (dict(nx=480, ny=1301, prec="fp64"), dict(nx=840, ny=1070, prec="fp32")):
+        cmd = [lh.sim(**case)] + [f"{op} {n}" for n in range(1, 24) for op in ("step", "capture")]
+        res = lh.drive(exe, cmd)
+        assert all(l.grid > 0 for r in res for l in r.launches)
+        assert any("12block_kernel" in l.kernel for r in res for l in r.launches)
+        seen += sum("march_kernel" in l.kernel for r in res for l in r.launches)
+    assert seen > 0
