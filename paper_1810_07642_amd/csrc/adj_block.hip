@@ -48,7 +48,7 @@ bool plan_adj_block(const tflbm_sim *s, BlockPlan &best) {
   if (best.ns == 0) return false;
   if (best.always) return true;
   best.limit = kAdjLimit[p.prec == kF64 ? 0 : 1][s->w1 ? 1 : 0] * m.march((double)s->adj_nstrips * p.ny, m.march2);
-  return best.ns >= 2 && t < best.limit;
+  return t < best.limit;
 }
 
 // Whether a call of nsteps reverse steps takes the plan, in k passes: not where all

@@ -19,7 +19,15 @@ extern template hipError_t launch_block_form<kF16S, true>(int, const BlockArgs &
 double best_plan(const TileModel &m, const BlockShape *shapes, int n, int nx, int ny, int extra,
                  const char *env, const char *env_shape, BlockPlan &best) {
   best = BlockPlan();
-  int ns_min = 1, ns_max = 9, only = -1;
+  // A pass of one step is no plan: there are as many launches as of the marching
+  // kernel's, and passes whose number cannot be made even or odd with that of its
+  // fused ones.  Nor may it stand in the way of two or more steps, which the model
+  // puts a few percent behind it at some sizes though they are faster (us per step,
+  // marching / one / two or more: FP16S at tau = 0.9 323x925 18.1 / 7.2 / 6.6,
+  // 1285x843 32.6 / 18.9 / 15.2) or, where one step is not taken, of the marching
+  // kernel (FP64 at tau = 0.9 450^2 9.4 / 8.6, 500^2 10.5 / 9.2; FP16S 212x1089 9.2 /
+  // 5.4; reverse, FP64 138x638 8.7 / 6.9).
+  int ns_min = 2, ns_max = 9, only = -1;
   if (const char *e = std::getenv(env)) {
     const int v = std::atoi(e);
     if (v <= 0) return 0.0;
@@ -119,7 +127,6 @@ bool plan_block(const tflbm_sim *s, BlockPlan &best) {
     best.limit = 1e30;
     return true;
   }
-  if (best.ns < 2 && !odd) return false;  // as many launches as the marching kernel's
   // a surface tension field stays with the marching kernels where that is near (FP32,
   // general stages, 808x1306: 25 us per step against 16)
   const bool gamma = s->kfield == kGammaKappa;

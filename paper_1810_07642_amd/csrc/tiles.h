@@ -73,8 +73,9 @@ struct BlockPlan {
   double limit = 0.0;   // modelled time per step from which on a call stays with the marching kernels
 };
 
-// The shape and steps per pass of the least modelled time per step, of n shapes,
-// and that time; TFLBM_<name> and TFLBM_<name>_SHAPE (`env`, `env_shape`) force both.
+// The shape and steps per pass (two or more) of the least modelled time per step, of n
+// shapes, and that time; TFLBM_<name> and TFLBM_<name>_SHAPE (`env`, `env_shape`) force
+// both, one step too.
 // best.ns = 0 where no shape serves or TFLBM_<name>=0.
 double best_plan(const TileModel &m, const BlockShape *shapes, int n, int nx, int ny, int extra,
                  const char *env, const char *env_shape, BlockPlan &best);

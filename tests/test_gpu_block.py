@@ -106,3 +106,28 @@ def test_calls_that_leave_the_plan_equal_single_steps_bitwise(prec, nx, ny):
         got, _ = run(prec, ny, nx, "theta", steps, {}, p)
         for a, b in zip(got, ref):
             assert torch.equal(a, b), steps
+
+
+def test_odd_fp16s_calls_in_a_callers_graph():
+    """FP16S of odd width: a caller's own graph of three steps ends on the
+    buffer it started from, as with the marching kernel's two passes, so that
+    each replay advances the state like the eager call."""
+    p = dict(tau=0.9, gamma=0.01, g=1e-3, hstar=0.1, delta=1.0, ax=1e-5, href=0.4)
+    from paper_1810_07642_amd import Sim
+    h0, th = random_case(2622, 279, 63)
+    a, b = (Sim(279, 2622, "fp16s", **p).init(h0, th) for _ in range(2))
+    a.step(3)
+    b.step(3)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            a.step(3)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        graph.replay()
+        b.step(3)
+        torch.cuda.synchronize()
+        assert torch.equal(a.state_save(), b.state_save())
+    a.check()

@@ -58,3 +58,60 @@ def test_calls_that_leave_a_block_plan_launch_whole_grids(exe):
         assert any("12block_kernel" in l.kernel for r in res for l in r.launches)
         seen += sum("march_kernel" in l.kernel for r in res for l in r.launches)
     assert seen > 0
+
+
+NO_BLOCK = ["env TFLBM_BLOCK 0", "env TFLBM_MARCH 0", "env TFLBM_ADJ_BLOCK 0"]
+DEFAULT = ["env TFLBM_BLOCK", "env TFLBM_MARCH", "env TFLBM_ADJ_BLOCK"]
+
+
+def ends(exe, case, env, counts):
+    """The buffers that calls of `counts` steps, captures and reverse steps end on."""
+    cmd, at = list(env), []
+    for n in counts:
+        calls = [[f"step {n}", "read"], [f"capture {n}", "read"]]
+        if case.get("field") != "gamma":
+            calls.append(["capture 1", "seed", f"adj {n}", "finish"])
+        for c in calls:
+            cmd += [lh.sim(**case)] + c
+            at.append(len(cmd) - 1)
+    res = lh.drive(exe, cmd)
+    assert all(r.rc == 0 for r in res)
+    return [res[i].launches[0].src for i in at]
+
+
+# FP16S of odd width (one step per pass models best on the first three), and
+# lattices of every form that the block kernels, the passes of moments and the
+# marching kernels step
+PARITY = [dict(nx=279, ny=2622, prec="fp16s", tau=0.9), dict(nx=357, ny=2623, prec="fp16s", tau=0.9),
+          dict(nx=277, ny=2676, prec="fp16s", tau=0.9), dict(nx=901, ny=641, prec="fp16s"),
+          dict(nx=450, ny=450, prec="fp64", tau=0.9), dict(nx=64, ny=64, prec="fp64"),
+          dict(nx=1024, ny=1024, prec="fp64"), dict(nx=512, ny=512, prec="fp32"),
+          dict(nx=901, ny=641, prec="fp32", tau=1.2, field="gamma"), dict(nx=2048, ny=2048, prec="fp32"),
+          dict(nx=480, ny=1301, prec="fp64"), dict(nx=840, ny=1070, prec="fp32"),
+          dict(nx=512, ny=512, prec="fp32", n=10, m=4), dict(nx=4096, ny=4096, prec="fp64")]
+
+
+@pytest.mark.parametrize("case", PARITY, ids=lambda c: "_".join(str(v) for v in c.values()))
+def test_calls_end_on_the_marching_kernels_buffer(exe, case):
+    """A caller's own graph of a call can be replayed where the call ends on
+    the buffer it started from: every plan ends on the marching kernel's."""
+    counts = range(1, 13)
+    assert ends(exe, case, DEFAULT, counts) == ends(exe, case, NO_BLOCK, counts)
+
+
+@pytest.mark.parametrize("case", [dict(nx=450, ny=450, prec="fp64", tau=0.9), dict(nx=500, ny=500, prec="fp64", tau=0.9),
+                                  dict(nx=138, ny=1335, prec="fp64", tau=0.9), dict(nx=212, ny=1089, prec="fp16s", tau=0.9),
+                                  dict(nx=1359, ny=228, prec="fp16s", tau=0.9)],
+                         ids=lambda c: "_".join(str(v) for v in c.values()))
+def test_one_step_per_pass_drops_no_block_plan(exe, case):
+    """Where a pass of one step models best, the block kernel still takes the
+    best plan of several steps that beats the marching kernel."""
+    res = lh.drive(exe, [lh.sim(**case), "spp", "step 12"])
+    assert res[1].rc >= 2
+    assert all("block_kernel" in l.kernel for l in res[2].launches) and len(res[2].launches) <= 6
+
+
+def test_one_step_per_pass_drops_no_reverse_block_plan(exe):
+    for case in (dict(nx=64, ny=1007, prec="fp64"), dict(nx=434, ny=925, prec="fp32"), dict(nx=804, ny=515, prec="fp32")):
+        res = lh.drive(exe, [lh.sim(**case), "capture 12", "seed", "adj 12"])
+        assert all("adj_block_kernel" in l.kernel for l in res[3].launches) and len(res[3].launches) <= 6, case
