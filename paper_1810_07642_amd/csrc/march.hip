@@ -32,11 +32,22 @@ static int strip_columns(int prec, int kind) {
 // two / three: FP32 1536^2 18.5 / 19.4, 2048^2 23.1 / 24.2, 4096^2 74.9 / 68.5;
 // FP64 1536^2 26.4 / 26.9, 2048^2 35.7 / 39.4, 4096^2 149.4 / 132.5.
 constexpr int64_t kMarch3MinSites = 8000000;
+// No such passes on lattices of fewer strip rows: there a tile's time is its chain
+// of rows, which passes of two steps make longer than step_kernel's plan of one step
+// per pass (api.hip).  (These lattices come here where the block kernel does not
+// serve the exponents.)  Measured, us per step of calls of 10 steps, step_kernel /
+// moments, exponents (10, 4): FP32 64^2 6.2 / 9.9, 256^2 7.1 / 10.5, 512^2 (2560 strip
+// rows) 10.4 / 11.9; FP64 64^2 4.8 / 7.2, 256^2 7.2 / 9.5, 384^2 (3456) 9.2 / 9.4.  From
+// 3000 to 5000 strip rows they are 10 % faster to 10 % slower, by the rows of a chunk
+// and with captures; in 60 lattices of 5500 to 7000 none is slower (10 steps 2 to 13 %
+// faster, 64 steps 4 to 22 %).
+constexpr int64_t kMarchMinStripRows = 5400;
 
 void plan_march(tflbm_sim *s) {
   s->march_ns = 0;
   if (!s->w1 || s->p.prec == kF16S || s->kfield == kGammaKappa || s->fuse != 0) return;
-  s->march_ns = (int64_t)s->p.nx * s->p.ny >= kMarch3MinSites ? 3 : 2;
+  if ((int64_t)s->nstrips * s->p.ny >= kMarchMinStripRows)
+    s->march_ns = (int64_t)s->p.nx * s->p.ny >= kMarch3MinSites ? 3 : 2;
   if (const char *e = std::getenv("TFLBM_MARCH")) s->march_ns = std::atoi(e) <= 0 ? 0 : (std::atoi(e) >= 3 ? 3 : 2);
 }
 

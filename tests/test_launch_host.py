@@ -115,3 +115,17 @@ def test_one_step_per_pass_drops_no_reverse_block_plan(exe):
     for case in (dict(nx=64, ny=1007, prec="fp64"), dict(nx=434, ny=925, prec="fp32"), dict(nx=804, ny=515, prec="fp32")):
         res = lh.drive(exe, [lh.sim(**case), "capture 12", "seed", "adj 12"])
         assert all("adj_block_kernel" in l.kernel for l in res[3].launches) and len(res[3].launches) <= 6, case
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_passes_of_moments_stay_off_small_lattices(exe, prec):
+    """Exponents that the block kernel does not serve, at tau = 1: lattices
+    whose tiles are a chain of rows run the passes of the plan without moments."""
+    def names(nx, ny, env):
+        res = lh.drive(exe, list(env) + [lh.sim(nx, ny, prec, n=10, m=4), "step 10", "capture 16", "spp"])
+        return [l.kernel for r in res for l in r.launches], res[-1].rc
+    for nx, ny in ((64, 64), (128, 128), (256, 256), (90, 2500), (900, 200)):
+        plain, spp = names(nx, ny, NO_BLOCK)
+        got, got_spp = names(nx, ny, DEFAULT)
+        assert got == plain and got_spp == spp and not any("march_kernel" in n for n in got), (nx, ny)
+    assert any("march_kernel" in n for n in names(1024, 1024, DEFAULT)[0])
