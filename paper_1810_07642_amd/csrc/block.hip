@@ -147,7 +147,8 @@ bool block_takes(const tflbm_sim *s, int64_t nsteps, int64_t k, bool capture) {
   const int f = form_of(p.prec), extra = extra_columns(p.prec);
   int n = 0;
   const BlockShape &sh = shapes_of(p.prec, s->w1, n)[b.shape];
-  const int kind = (s->w1 && s->kfield != kGammaKappa ? kOmega1 : kGeneral) + (capture ? 1 : 0);
+  // (a surface tension field's calls hand over no moments by the marching kernels)
+  const int kind = capture ? (s->w1 ? kOmega1Cap : kGeneralCap) : (s->w1 && s->kfield != kGammaKappa ? kOmega1 : kGeneral);
   const int length = nsteps <= 2 ? 0 : (nsteps < 10 && (nsteps & 1) ? 1 : 2);
   const bool one_round = Tiles(p.nx, p.ny, sh, (int)((nsteps + k - 1) / k), extra).ntiles <= 256;
   const double limit = one_round && !(kind == kOmega1Cap && length == 0) ? 1.0 : kLimit[f][kind][length];
