@@ -109,16 +109,18 @@ void plan_launches(tflbm_sim *s) {
   s->rows3 = choose_rows(ny, s->nstrips, occ3 * cus, kMinRowsStep, "TFLBM_ROWS3");
   s->ntiles3 = s->nstrips * ((ny + s->rows3 - 1) / s->rows3);
   s->per_xcd3 = (s->ntiles3 + 7) / 8;
-  // Two fused steps per pass pay off once the one-step plan can no longer give
-  // every row a tile of its own in one round of resident wavefronts: below
-  // that a tile's time is its chain of rows, 5 for one step against 11 per
-  // two fused steps, each of those twice the work.  Measured per step at FP32:
-  // 128^2 5.4 vs 6.4 us, 256^2 6.0 vs 6.8, 512^2 9.2 vs 9.4; from 768^2 on
-  // the fused pass wins.  FP16S, whose rows take longer to decode, gains from
+  // Two fused steps per pass pay off above about 12 strip rows per CU (3072): below
+  // that a tile's time is its chain of rows, 5 for one step against 11 per two
+  // fused steps, each of those twice the work.  Measured per step at FP32:
+  // 128^2 5.4 vs 6.4 us, 256^2 6.0 vs 6.8, 512^2 9.4 vs 11.1; from 768^2 on
+  // the fused pass wins.  A count of its own, not the one-step kernel's resident
+  // wavefronts, which change with its registers: the number of passes decides on
+  // which buffer a call ends, hence which calls a caller's own graph can replay.
+  // FP16S, whose rows take longer to decode, gains from
   // one step per pass up to about 24 one-row tiles per CU (g = 0, per step:
   // 512^2 10.0 vs 12.0 us, 768^2 12.4 vs 14.1; 1024^2 18.5 vs 17.9; with
   // g != 0 likewise 512^2 10.9 vs 12.9, 768^2 13.7 vs 15.1).
-  const int64_t one_row_tiles = s->p.prec == kF16S ? 24LL * cus : (int64_t)occ1 * cus;
+  const int64_t one_row_tiles = (s->p.prec == kF16S ? 24LL : 12LL) * cus;
   s->fuse_fits = (int64_t)s->nstrips * ny > one_row_tiles;
   // Three steps per pass: with the omega = 1 stages, on lattices with long
   // enough chunks (kFuse3MinRowsPerSlot).

@@ -131,3 +131,28 @@ def test_odd_fp16s_calls_in_a_callers_graph():
         torch.cuda.synchronize()
         assert torch.equal(a.state_save(), b.state_save())
     a.check()
+
+
+@pytest.mark.parametrize("block", [True, False])
+def test_fp32_calls_of_two_steps_in_a_callers_graph(block):
+    """2560 strip rows: two steps are two passes, of either kernel, so that a
+    caller's own graph of them ends on the buffer it started from."""
+    from paper_1810_07642_amd import Sim
+    p = dict(tau=1.0, gamma=0.01, hstar=0.1, delta=1.0, ax=1e-5, href=0.4, **({} if block else dict(n=10, m=4)))
+    h0, th = random_case(512, 512, 64)
+    a, b = (Sim(512, 512, "fp32", **p).init(h0, th) for _ in range(2))
+    a.step(2)
+    b.step(2)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            a.step(2)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        graph.replay()
+        b.step(2)
+        torch.cuda.synchronize()
+        assert torch.equal(a.state_save(), b.state_save())
+    a.check()

@@ -129,3 +129,13 @@ def test_passes_of_moments_stay_off_small_lattices(exe, prec):
         got, got_spp = names(nx, ny, DEFAULT)
         assert got == plain and got_spp == spp and not any("march_kernel" in n for n in got), (nx, ny)
     assert any("march_kernel" in n for n in names(1024, 1024, DEFAULT)[0])
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_fused_passes_begin_at_a_lattice_size_of_their_own(exe, prec):
+    """The steps per pass, and with them the buffer a call ends on, do not
+    change with the registers of the one-step kernel (its resident workgroups)."""
+    for occupancy in (8, 12, 16):
+        for rows, spp in ((2560, 1), (3072, 1), (3073, 2)):
+            res = lh.drive(exe, NO_BLOCK + [f"occupancy {occupancy}", lh.sim(40, rows, prec, tau=0.9), "spp", "step 2"])
+            assert res[-2].rc == spp and len(res[-1].launches) == 2 // spp, (occupancy, rows)
