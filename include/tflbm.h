@@ -200,7 +200,9 @@ int tflbm_init_fields(tflbm_sim *sim, const double *d_h0, const double *d_theta,
  * stream the handle creates for it.
  * The results are the same bits as with plain launches.  Where `stream` is
  * itself being captured, or capturing fails, the steps are launched one by
- * one. */
+ * one.  Where a launch fails (TFLBM_EHIP) part of the steps were taken
+ * (tflbm_step_count); with tau = 1 the state may be lost then, and every call
+ * that reads it returns TFLBM_ESTATE until tflbm_init or tflbm_state_load. */
 int tflbm_step(tflbm_sim *sim, int64_t nsteps, tflbm_stream_t stream);
 
 /* Number of step graphs the handle holds (0, 1 or 2: one per starting buffer

@@ -343,6 +343,7 @@ int tflbm_bind(tflbm_sim *sim, void *d_ws, size_t bytes) {
   drop_graphs(sim);
   sim->ws = (char *)d_ws;
   sim->initialised = false;
+  sim->lost = false;
   sim->adj_seeded = false;
   sim->cur = 0;
   sim->steps = 0;
@@ -375,6 +376,7 @@ int tflbm_init_fields(tflbm_sim *sim, const double *d_h0, const double *d_theta,
   sim->cur = 0;
   sim->steps = 0;
   sim->initialised = true;
+  sim->lost = false;
   sim->adj_seeded = false;
   return TFLBM_OK;
 }
@@ -409,7 +411,10 @@ static int launch_block_steps(tflbm_sim *sim, int64_t nsteps, int64_t k, void *d
     A.in_mom = sim->w1 && i > 0;
     A.out_mom = sim->w1 && i + 1 < k;
     const int rc = hip_status(sim, launch_block(sim->p.prec, sim->w1, sim->block.shape, A, st));
-    if (rc) return rc;
+    if (rc) {
+      sim->lost = A.in_mom != 0;
+      return rc;
+    }
     sim->cur ^= 1;
     sim->steps += ns;
     done += ns;
@@ -434,7 +439,10 @@ static int launch_march_steps(tflbm_sim *sim, const MarchSplit &sp, void *d_capt
     A.ntiles = m.ntiles;
     A.per_xcd = m.per_xcd;
     const int rc = hip_status(sim, launch_march(sim->p.prec, kind, A, sim->kfield, d_capture != nullptr, nullptr, st));
-    if (rc) return rc;
+    if (rc) {
+      sim->lost = i > 0;
+      return rc;
+    }
     sim->cur ^= 1;
     sim->steps += ns;
     done += ns;
@@ -495,6 +503,7 @@ static bool graph_block(tflbm_sim *sim, hipStream_t st, int &rc) {
       if (g) (void)hipGraphDestroy(g);
       sim->cur = cur0;  // capturing ran nothing
       sim->steps = steps0;
+      sim->lost = false;
     }
     if (!ok) {
       ex = nullptr;
@@ -511,7 +520,7 @@ static bool graph_block(tflbm_sim *sim, hipStream_t st, int &rc) {
 
 static int run_steps(tflbm_sim *sim, int64_t nsteps, void *d_capture, tflbm_stream_t stream) {
   if (!sim || nsteps < 0) return TFLBM_EINVAL;
-  if (!sim->initialised) return TFLBM_ESTATE;
+  if (!has_state(sim)) return TFLBM_ESTATE;
   hipStream_t st = (hipStream_t)stream;
   int64_t done = 0;
   if (d_capture == nullptr && sim->graphs) {
@@ -553,7 +562,7 @@ int tflbm_step_graphs(const tflbm_sim *sim) {
 
 int tflbm_read(const tflbm_sim *sim, double *d_h, double *d_ux, double *d_uy, tflbm_stream_t stream) {
   if (!sim) return TFLBM_EINVAL;
-  if (!sim->initialised) return TFLBM_ESTATE;
+  if (!has_state(sim)) return TFLBM_ESTATE;
   if (!d_h && !d_ux && !d_uy) return TFLBM_OK;
   StepArgs A = make_step_args(sim);
   return hip_status(sim, launch_read(sim->p.prec, A, d_h, d_ux, d_uy, (hipStream_t)stream));
@@ -561,7 +570,7 @@ int tflbm_read(const tflbm_sim *sim, double *d_h, double *d_ux, double *d_uy, tf
 
 int tflbm_mass(const tflbm_sim *sim, double *h_mass, tflbm_stream_t stream) {
   if (!sim || !h_mass) return TFLBM_EINVAL;
-  if (!sim->initialised) return TFLBM_ESTATE;
+  if (!has_state(sim)) return TFLBM_ESTATE;
   hipStream_t st = (hipStream_t)stream;
   StepArgs A = make_step_args(sim);
   int rc = hip_status(sim, launch_mass(sim->p.prec, A, (double *)(sim->ws + sim->off_part), sim->n_partials,
@@ -574,7 +583,7 @@ int tflbm_mass(const tflbm_sim *sim, double *h_mass, tflbm_stream_t stream) {
 
 int tflbm_term_norms(const tflbm_sim *sim, double *h_norms, tflbm_stream_t stream) {
   if (!sim || !h_norms) return TFLBM_EINVAL;
-  if (!sim->initialised) return TFLBM_ESTATE;
+  if (!has_state(sim)) return TFLBM_ESTATE;
   hipStream_t st = (hipStream_t)stream;
   StepArgs A = make_step_args(sim);
   const int nb = terms_blocks(sim->p.nx, sim->p.ny, sim->n_partials);
@@ -611,7 +620,7 @@ static hipError_t copy_state(const void *src, void *dst, size_t bytes, hipStream
 
 int tflbm_state_save(const tflbm_sim *sim, void *d_dst, tflbm_stream_t stream) {
   if (!sim || !d_dst) return TFLBM_EINVAL;
-  if (!sim->initialised) return TFLBM_ESTATE;
+  if (!has_state(sim)) return TFLBM_ESTATE;
   const char *src = sim->ws + (sim->cur == 0 ? sim->off_a : sim->off_b);
   return hip_status(sim, copy_state(src, d_dst, sim->pop_bytes, (hipStream_t)stream));
 }
@@ -623,6 +632,7 @@ int tflbm_state_load(tflbm_sim *sim, const void *d_src, int64_t step, tflbm_stre
   const int rc = hip_status(sim, copy_state(d_src, dst, sim->pop_bytes, (hipStream_t)stream));
   if (rc) return rc;
   sim->steps = step;
+  sim->lost = false;
   return TFLBM_OK;
 }
 

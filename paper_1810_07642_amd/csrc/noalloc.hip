@@ -47,7 +47,7 @@ using namespace tflbm;
 
 extern "C" int tflbm_mass_noalloc(const tflbm_sim *sim, double *d_mass, tflbm_stream_t stream) {
   if (!sim || !d_mass) return TFLBM_EINVAL;
-  if (!sim->initialised) return TFLBM_ESTATE;
+  if (!has_state(sim)) return TFLBM_ESTATE;
   if (sim->n_partials < 1 || sim->n_partials > kScratchPartials) {
     sim->last_error = "the mass reduction needs more partial sums than the static scratch array holds (1024)";
     return TFLBM_EINVAL;

@@ -18,6 +18,7 @@ struct tflbm_sim {
   int n_partials = 0;
   char *ws = nullptr;     // bound device workspace
   bool initialised = false;
+  bool lost = false;      // a call ended on a launch error with moments in the current buffer
   int kfield = 0;         // FieldKind: kappa (theta field given at init) or the gamma-kappa pairs read per site
   int cur = 0;            // 0: buffer A holds the current populations
   int64_t steps = 0;
@@ -55,6 +56,9 @@ struct tflbm_sim {
 };
 
 namespace tflbm {
+
+// Whether the current buffer holds populations.
+inline bool has_state(const tflbm_sim *s) { return s->initialised && !s->lost; }
 
 // Bytes per element of the working type.
 inline int work_bytes(int prec) { return prec == kF64 ? 8 : 4; }

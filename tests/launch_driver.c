@@ -76,6 +76,7 @@ int main(void) {
   void *const ws = (void *)0x100000000000ull, *const cap = (void *)0x200000000000ull, *const adj = (void *)0x300000000000ull;
   double *const h0 = (double *)0x400000000000ull;
   char line[256], cmd[32];
+  double mass, norms[8];
   tflbm_sim *s = NULL;
   while (fgets(line, sizeof line, stdin)) {
     int rc = 0, used = 0;
@@ -106,6 +107,10 @@ int main(void) {
     } else if (!strcmp(cmd, "step")) rc = tflbm_step(s, atoll(a), NULL);
     else if (!strcmp(cmd, "capture")) rc = tflbm_step_capture(s, atoll(a), cap, NULL);
     else if (!strcmp(cmd, "read")) rc = tflbm_read(s, h0, NULL, NULL, NULL);
+    else if (!strcmp(cmd, "mass")) rc = tflbm_mass(s, &mass, NULL);
+    else if (!strcmp(cmd, "mass_noalloc")) rc = tflbm_mass_noalloc(s, h0, NULL);
+    else if (!strcmp(cmd, "terms")) rc = tflbm_term_norms(s, norms, NULL);
+    else if (!strcmp(cmd, "check")) rc = tflbm_check(s, NULL);
     else if (!strcmp(cmd, "save")) rc = tflbm_state_save(s, cap, NULL);
     else if (!strcmp(cmd, "load")) rc = tflbm_state_load(s, cap, 0, NULL);
     else if (!strcmp(cmd, "seed")) rc = tflbm_adj_seed(s, adj, h0, NULL);

@@ -139,3 +139,36 @@ def test_fused_passes_begin_at_a_lattice_size_of_their_own(exe, prec):
         for rows, spp in ((2560, 1), (3072, 1), (3073, 2)):
             res = lh.drive(exe, NO_BLOCK + [f"occupancy {occupancy}", lh.sim(40, rows, prec, tau=0.9), "spp", "step 2"])
             assert res[-2].rc == spp and len(res[-1].launches) == 2 // spp, (occupancy, rows)
+
+
+ESTATE, EHIP = -5, -3
+READERS = ["read", "mass", "mass_noalloc", "terms", "save", "step 1", "capture 1"]
+
+
+@pytest.mark.parametrize("case", [dict(nx=512, ny=512, prec="fp32"), dict(nx=128, ny=128, prec="fp16s"),
+                                  dict(nx=1024, ny=1024, prec="fp64"), dict(nx=4096, ny=4096, prec="fp32")],
+                         ids=lambda c: "_".join(str(v) for v in c.values()))
+@pytest.mark.parametrize("call", ["step 20", "capture 20"])
+def test_state_is_lost_where_a_launch_fails_between_passes_of_moments(exe, case, call):
+    """The current buffer holds moments then: no call takes them for
+    populations, until a new state comes."""
+    first = lh.sim(**case)
+    cmd = [first, "fail 1", call] + READERS + ["check", "load", "read", "step 20", "read"]
+    rc = [r.rc for r in lh.drive(exe, cmd)]
+    assert rc[2] == EHIP and rc[3:3 + len(READERS)] == [ESTATE] * len(READERS)
+    assert rc[3 + len(READERS):] == [0] * 5
+    # after a failing first launch the state is the one before the call; a new init brings one
+    assert [r.rc for r in lh.drive(exe, [first, "fail 0", call] + READERS)] == [0, 0, EHIP] + [0] * len(READERS)
+    assert [r.rc for r in lh.drive(exe, [first, "fail 1", call, "init", "read"])] == [0, 0, EHIP, 0, 0]
+
+
+def test_state_stays_where_passes_hand_over_populations(exe):
+    for case in (dict(nx=512, ny=512, prec="fp32", tau=0.9), dict(nx=1024, ny=1024, prec="fp64", tau=0.9)):
+        rc = [r.rc for r in lh.drive(exe, [lh.sim(**case), "fail 1", "step 20", "read", "step 3", "read"])]
+        assert rc == [0, 0, EHIP, 0, 0, 0]
+
+
+def test_a_capture_that_fails_loses_no_state(exe):
+    """The library's own step graphs: nothing has run, the steps are launched."""
+    res = lh.drive(exe, [lh.sim(128, 128, "fp64"), "step 256", "fail 1", "step 64", "read"])
+    assert [r.rc for r in res] == [0] * 5 and len(res[3].launches) > 1
