@@ -41,6 +41,8 @@ def test_reverse_calls_take_the_faster_kernel(exe, case, steps, block):
     (dict(nx=1232, ny=911, prec="fp32", tau=0.9), "step 4", True),        # 17.9 / 16.4
     (dict(nx=1157, ny=327, prec="fp32", tau=0.9), "capture 4", True),     # 12.1 / 9.2
     (dict(nx=568, ny=1446, prec="fp16s"), "capture 2", False),            # 13.3 / 14.0
+    (dict(nx=161, ny=1164, prec="fp32", tau=0.9), "step 2", True),        # 11.4 / 7.0, two passes
+    (dict(nx=421, ny=590, prec="fp32", tau=0.9), "capture 3", True),      # 11.7 / 7.5
     (dict(nx=128, ny=128, prec="fp32"), "capture 3", True),
     (dict(nx=128, ny=128, prec="fp32"), "step 2", False)])
 def test_forward_calls_take_the_faster_kernel(exe, case, call, block):
@@ -172,3 +174,17 @@ def test_a_capture_that_fails_loses_no_state(exe):
     """The library's own step graphs: nothing has run, the steps are launched."""
     res = lh.drive(exe, [lh.sim(128, 128, "fp64"), "step 256", "fail 1", "step 64", "read"])
     assert [r.rc for r in res] == [0] * 5 and len(res[3].launches) > 1
+
+
+@pytest.mark.parametrize("march,middle", [(2, "ELi2ELb1ELb1"), (3, "ELi3ELb1ELb1")])
+def test_captured_calls_split_into_passes_of_moments(exe, march, middle):
+    """The step counts whose captures are compared bit for bit on the GPU:
+    10 and 23 steps split, with a middle pass of either kind, 9 do not."""
+    for prec in ("fp64", "fp32"):
+        for nx, ny in ((330, 40), (433, 20), (37, 23)):
+            env = ["env TFLBM_BLOCK 0", f"env TFLBM_MARCH {march}"]
+            res = lh.drive(exe, env + [lh.sim(nx, ny, prec), "capture 10", "capture 23", "capture 9"])
+            for r in res[-3:-1]:
+                assert all("march_kernel" in l.kernel for l in r.launches) and len(r.launches) >= 4
+            assert any(middle in l.kernel for r in res[-3:-1] for l in r.launches)
+            assert not any("march_kernel" in l.kernel for l in res[-1].launches)
