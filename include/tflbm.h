@@ -265,7 +265,10 @@ int tflbm_check(const tflbm_sim *sim, tflbm_stream_t stream);
  * a fixed order (deterministic).  TFLBM_ESTATE before tflbm_init. */
 int tflbm_term_norms(const tflbm_sim *sim, double *h_norms, tflbm_stream_t stream);
 
-/* Bytes of one population buffer (a checkpoint of the state). */
+/* Bytes of one population buffer (a checkpoint of the state).  Its records have
+ * padding that nothing reads and that not every kernel writes: two checkpoints of
+ * one state are equal byte for byte where the workspace was zeroed before
+ * tflbm_init. */
 size_t tflbm_state_bytes(const tflbm_sim *sim);
 
 /* (async) Copies the current populations into d_dst (tflbm_state_bytes bytes). */
@@ -288,7 +291,8 @@ int tflbm_state_load(tflbm_sim *sim, const void *d_src, int64_t step, tflbm_stre
 
 /* Bytes of one step's capture: h, h u_x, h u_y at the start of the step, in
  * the working type, laid out in records of the population records' columns
- * (internal layout, read only by tflbm_adj_step). */
+ * (internal layout, read only by tflbm_adj_step).  The records' padding, which
+ * nothing reads, is zeroed by some kernels and left as it was by others. */
 size_t tflbm_capture_bytes(const tflbm_sim *sim);
 
 /* (async) Like tflbm_step, and also writes the capture of step i

@@ -185,3 +185,14 @@ def check_err(case, err, apriori):
 
 def banner(msg):
     print(msg, flush=True)
+
+
+def captured_moments(cap, prec, ny, nx, steps):
+    """The bytes of the moments in a buffer of `steps` captures, without the
+    records' padding and the columns past nx: [steps][ny][nx][3][bytes]."""
+    es = 8 if prec == "fp64" else 4
+    cols = {"fp64": 46, "fp32": 108, "fp16s": 116}[prec]
+    rec = -(-3 * cols * es // 128) * 128
+    nblk = -(-nx // cols)
+    r = cap.view(steps, ny, nblk, rec)[..., :3 * cols * es].reshape(steps, ny, nblk, 3, cols, es)
+    return r.permute(0, 1, 2, 4, 3, 5).reshape(steps, ny, nblk * cols, 3, es)[:, :, :nx]

@@ -7,7 +7,7 @@ import os
 import pytest
 import torch
 
-from gpu_common import banner, random_case
+from gpu_common import banner, captured_moments, random_case
 from test_gpu_gamma import gamma_field
 
 pytestmark = pytest.mark.gpu
@@ -156,3 +156,29 @@ def test_fp32_calls_of_two_steps_in_a_callers_graph(block):
         torch.cuda.synchronize()
         assert torch.equal(a.state_save(), b.state_save())
     a.check()
+
+
+@pytest.mark.parametrize("prec,tau,shape", CASES)
+def test_captures_equal_marching_kernel_bitwise(prec, tau, shape):
+    """The captured moments, on buffers that held something else; whole
+    records (108, 46, 116 columns) and one column less."""
+    from paper_1810_07642_amd import Sim
+    p = dict(tau=tau, gamma=0.01, g=1e-3, hstar=0.1, delta=1.0, ax=1e-5, ay=-1e-5, href=0.4)
+    for (ny, nx) in ((23, 37), (40, 216), (40, 232), (33, 92), (50, 231), (70, 340)):
+        banner(f"captures by the block kernel: {prec} tau={tau} shape {shape} {ny}x{nx}")
+        h0, th = random_case(ny, nx, 65)
+
+        def capture(env):
+            os.environ.update(env)
+            try:
+                sim = Sim(nx, ny, prec, **p).init(h0, th)
+            finally:
+                for k in env:
+                    del os.environ[k]
+            cap = torch.full((5 * sim.capture_bytes(),), 0xA5, dtype=torch.uint8, device=sim.device)
+            sim.step_capture(5, cap)
+            sim.check()
+            return captured_moments(cap, prec, ny, nx, 5).cpu()
+
+        ref = capture({"TFLBM_FUSE": "1"})
+        assert torch.equal(capture({"TFLBM_BLOCK": "2", "TFLBM_BLOCK_SHAPE": str(shape)}), ref), (ny, nx)

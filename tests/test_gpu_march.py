@@ -7,7 +7,7 @@ import os
 import pytest
 import torch
 
-from gpu_common import banner, random_case
+from gpu_common import banner, captured_moments, random_case
 
 pytestmark = pytest.mark.gpu
 
@@ -81,3 +81,38 @@ def test_passes_of_moments_in_a_callers_graph(prec):
         torch.cuda.synchronize()
         assert torch.equal(a.state_save(), b.state_save())
     a.check()
+
+
+# steps of a call with captures: 10 and 23 split into passes of moments, with
+# middle passes of two and of three steps and either kind of last pass; 9 does not
+CAPTURE_STEPS = (10, 23, 9)
+# three records and more (108 FP32, 46 FP64 columns): whole ones, and one column
+# more or less; narrower than a strip
+CAPTURE_LATTICES = [(40, 330), (33, 432), (20, 433), (50, 691), (70, 150), (23, 37)]
+
+
+@pytest.mark.parametrize("g", [1e-3, 0.0])
+@pytest.mark.parametrize("field", [True, False])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_captures_of_passes_of_moments_equal_single_steps_bitwise(prec, field, g):
+    """The captured moments, on buffers that held something else."""
+    p = dict(tau=1.0, gamma=0.01, g=g, hstar=0.1, delta=1.0, ax=1e-5, ay=-1e-5, href=0.4)
+
+    def captures(sim):
+        out = []
+        for n in CAPTURE_STEPS:
+            cap = torch.full((n * sim.capture_bytes(),), 0xA5, dtype=torch.uint8, device=sim.device)
+            sim.step_capture(n, cap)
+            out += [captured_moments(cap, prec, sim.ny, sim.nx, n).cpu(), sim.state_save().cpu()]
+        sim.check()
+        return out
+
+    for (ny, nx) in CAPTURE_LATTICES:
+        banner(f"captures of passes of moments: {prec} {ny}x{nx} field={field} g={g}")
+        ref = captures(make(prec, ny, nx, field, {"TFLBM_FUSE": "1"}, p))
+        for ns, rows in (("2", None), ("3", None), ("3", "9"), ("2", "7")):
+            env = {"TFLBM_BLOCK": "0", "TFLBM_MARCH": ns}
+            if rows:
+                env["TFLBM_MARCH_ROWS"] = rows
+            for a, b in zip(captures(make(prec, ny, nx, field, env, p)), ref):
+                assert torch.equal(a, b), (ny, nx, ns, rows)
