@@ -163,19 +163,32 @@ def step_kernel_name(sim, prec):
     return f"{name}<{prec}, kappa field, {sim.steps_per_pass} fused steps, omega = 1>"
 
 
-def roofline_block(kernel, bytes_per_launch, launch_ms, traffic, ceiling_gbs, steps_per_launch=2):
+def per_step_equivalent(prec, steps, sites, ms):
+    """GB/s if every step were a pass of its own: a pass's bytes per step and a
+    call's ends once."""
+    return round((BYTES_PER_SITE[prec] * steps + CALL_BYTES[prec]) * sites / (ms * 1e-3) / 1e9, 1)
+
+
+def roofline_block(kernel, bytes_per_launch, launch_ms, traffic, ceiling_gbs, steps_per_launch=2, pass_bytes=None,
+                   bound="hbm"):
     """Roofline position of one kernel: its algorithmic bytes per launch over
     its launch time, against the HBM peak (frac) and the record-copy ceiling;
     `traffic` = (measured HBM bytes per launch, steps per launch) from the
-    committed counter summary, or None."""
+    committed counter summary, or None.  `pass_bytes`: the algorithmic bytes of
+    the launches that the counters saw, where they are not those that
+    bytes_per_launch and launch_ms are the mean of (a call's first and last pass
+    move more): the counters' ratio is to them, and no rate is given.  `bound`:
+    what limits the kernel as measured, whatever its fraction of the
+    HBM peak."""
     achieved = bytes_per_launch / (launch_ms * 1e-3) / 1e9
-    blk = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+    same = pass_bytes is None or pass_bytes == bytes_per_launch
+    blk = {"bound": bound, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": round(achieved / HBM_PEAK_GBS, 4),
-           "traffic": None if traffic is None else round(traffic[0] / (launch_ms * 1e-3) / 1e9, 1),
+           "traffic": None if traffic is None or not same else round(traffic[0] / (launch_ms * 1e-3) / 1e9, 1),
            "kernel": kernel, "bytes_per_launch": int(bytes_per_launch), "steps_per_launch": steps_per_launch,
            "launch_us": round(launch_ms * 1e3, 2)}
     if traffic is not None:
-        blk["traffic_over_algorithmic"] = round(traffic[0] / bytes_per_launch, 4)
+        blk["traffic_over_algorithmic"] = round(traffic[0] / (bytes_per_launch if same else pass_bytes), 4)
     if ceiling_gbs:
         blk["ceiling"] = {"GBps": round(ceiling_gbs, 1), "what": "record copy (tflbm_state_save) of the same buffer",
                           "frac_of_ceiling": round(achieved / ceiling_gbs, 4)}
@@ -505,8 +518,9 @@ def main():
     spp64 = sims["fp64"].steps_per_pass
     launch_ms = ms64 / launches(args.steps, spp64)
     roof = roofline_block(step_kernel_name(sims["fp64"], "fp64"), launch_bytes("fp64", args.steps, spp64, sites),
-                          launch_ms, committed_traffic("fp64"), ceil_gbs, steps_per_launch=spp64)
-    roof["per_step_equivalent_GBps"] = round(BYTES_PER_SITE["fp64"] * sites / (ms_step * 1e-3) / 1e9, 1)
+                          launch_ms, committed_traffic("fp64"), ceil_gbs, steps_per_launch=spp64,
+                          pass_bytes=BYTES_PER_SITE["fp64"] * sites, bound="valu")
+    roof["per_step_equivalent_GBps"] = per_step_equivalent("fp64", args.steps, sites, ms64)
     line = {
         "metric": "D2Q9 thin-film MLUPS, % HBM roofline, FP32/FP64 speedup, adjoint/forward time",
         "value": round(mlups, 1),
@@ -542,10 +556,9 @@ def main():
                            "steps_timed": EXTRA_STEPS, "href": HREF[prec], "steps_per_pass": spp,
                            "roofline": roofline_block(step_kernel_name(sims[prec], prec),
                                                       launch_bytes(prec, EXTRA_STEPS, spp, sites), lm,
-                                                      committed_traffic(prec),
-                                                      ceil_gbs, steps_per_launch=spp)}
-            forms[prec]["roofline"]["per_step_equivalent_GBps"] = round(
-                BYTES_PER_SITE[prec] * sites / (ms / EXTRA_STEPS * 1e-3) / 1e9, 1)
+                                                      committed_traffic(prec), ceil_gbs, steps_per_launch=spp,
+                                                      pass_bytes=BYTES_PER_SITE[prec] * sites, bound="valu")}
+            forms[prec]["roofline"]["per_step_equivalent_GBps"] = per_step_equivalent(prec, EXTRA_STEPS, sites, ms)
         for prec in ("fp32", "fp16s"):
             forms[prec]["speedup_over_fp64"] = round(forms[prec]["mlups"] / forms["fp64"]["mlups"], 3)
         extras["forms"] = forms

@@ -75,6 +75,20 @@ def test_roofline_block_is_a_fraction_of_the_peak():
     assert bench.launches(21, 3) == 7 and bench.launches(20, 3) == 7 and bench.launches(24, 3) == 8
 
 
+@pytest.mark.parametrize("form", ["fp64", "fp32", "fp16s"])
+@pytest.mark.parametrize("steps", [20, 400])
+def test_traffic_is_compared_with_the_bytes_of_the_same_pass(form, steps):
+    """The counters saw passes between two others; a call's mean launch moves
+    more where its first and last pass do.  No ratio below 1, and no rate of one
+    kind of launch over the time of another."""
+    sites, spp = 4096 * 4096, bench.committed_traffic(form)[1]
+    mean = bench.launch_bytes(form, steps, spp, sites)
+    blk = bench.roofline_block("k", mean, 0.4, bench.committed_traffic(form), None, pass_bytes=bench.BYTES_PER_SITE[form] * sites)
+    assert 1.0 <= blk["traffic_over_algorithmic"] <= 1.5
+    assert blk["traffic"] is None if bench.CALL_BYTES[form] else blk["traffic"] >= blk["achieved"]
+    assert bench.per_step_equivalent(form, steps, sites, 1.0) >= round(bench.BYTES_PER_SITE[form] * steps * sites / 1e6, 1)
+
+
 def test_more_than_one_gpu_is_refused():
     root = os.path.dirname(os.path.abspath(bench.__file__))
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True,
