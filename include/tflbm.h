@@ -139,13 +139,15 @@ int tflbm_check_params(const tflbm_params *p);
  * TFLBM_ROWS3, TFLBM_ADJ_ROWS, TFLBM_ADJ_ROWS2 (rows per chunk of the one-,
  * two- and three-step kernels),
  * TFLBM_BLOCK=0 or n (read at tflbm_init: never the block kernel, or always,
- * with at most n steps per pass; by default on lattices where it is faster
- * than the marching kernels, unless one of the variables above asks for a
- * shape of theirs) and TFLBM_BLOCK_SHAPE (its tile shape),
+ * with at most n steps per pass, if a tile holds n steps (two to nine by form
+ * and stage), else never; by default on lattices and for calls where it is
+ * faster than the marching kernels, unless one of the variables above asks for
+ * a shape of theirs) and TFLBM_BLOCK_SHAPE (its tile shape),
  * TFLBM_ADJ_BLOCK and TFLBM_ADJ_BLOCK_SHAPE (the same for tflbm_adj_steps),
  * TFLBM_MARCH=0, 2 or 3 (read at tflbm_init: with tau = 1, whether the marching
  * kernels' passes of a call hand over moments instead of populations, and two or
- * three steps per such pass; by default by lattice size; the same bits) and
+ * three steps per such pass; by default by lattice size, from 5400 strip rows on;
+ * the same bits) and
  * TFLBM_MARCH_ROWS (rows per chunk of those passes),
  * TFLBM_GRAPH=0 or 1 (read at tflbm_init: whether tflbm_step replays blocks
  * of steps from graphs; by default on lattices of at most 2^20 sites). */
@@ -210,10 +212,12 @@ int tflbm_step(tflbm_sim *sim, int64_t nsteps, tflbm_stream_t stream);
 int tflbm_step_graphs(const tflbm_sim *sim);
 
 /* Most time steps one pass of tflbm_step advances on this handle (several
- * steps of eq. "LBE" applied to a tile before it is stored: up to 8 on
+ * steps of eq. "LBE" applied to a tile before it is stored: up to 9 on
  * lattices that the block kernel steps; else 1, 2 or 3, of which 3 needs tau = 1
- * and a lattice large enough for it to pay; TFLBM_FUSE and TFLBM_BLOCK
- * override); EINVAL for NULL, ESTATE before tflbm_init. */
+ * and a lattice large enough for it to pay, and is what passes that hand over
+ * moments reach, also where most of them take two; TFLBM_FUSE and TFLBM_BLOCK
+ * override).  A call's passes may be shorter, and calls too short for the block
+ * kernel to pay go to the others.  EINVAL for NULL, ESTATE before tflbm_init. */
 int tflbm_steps_per_pass(const tflbm_sim *sim);
 
 /* Number of steps taken since tflbm_init (host counter). */

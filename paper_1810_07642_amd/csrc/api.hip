@@ -126,8 +126,9 @@ void plan_launches(tflbm_sim *s) {
   // enough chunks (kFuse3MinRowsPerSlot).
   s->fuse3_fits = s->w1 && max_steps_per_pass(s->p.prec, s->w1) >= 3 && s->fuse_fits &&
                   (int64_t)s->nstrips * ny >= kFuse3MinRowsPerSlot * (int64_t)occ3 * cus;
-  // FP64 on such lattices: a two-step pass (the remainder of a call whose
-  // step count is not a multiple of three) runs the general stages' two-step
+  // FP64 on such lattices: a two-step pass of step_kernel (a call of two steps; without
+  // passes of moments also the remainder of a call whose step count is not a multiple
+  // of three) runs the general stages' two-step
   // kernel, which gives the same bits, plans the same chunks (eight
   // wavefronts per CU) and, with its uniform stores, is faster there (4096^2:
   // 570 against 613 us per launch).  Where the two-step pass is the main one

@@ -131,8 +131,9 @@ bool plan_block(const tflbm_sim *s, BlockPlan &best) {
     best.limit = 1e30;
     return true;
   }
-  // a surface tension field stays with the marching kernels where that is near (FP32,
-  // general stages, 808x1306: 25 us per step against 16)
+  // a surface tension field, whose second value per site the model leaves out, stays
+  // with the marching kernels where that is near (taken from one FP32 lattice, general
+  // stages, 808x1306: 25 us per step against 16; the other forms keep the same line)
   const bool gamma = s->kfield == kGammaKappa;
   best.limit = m.march((double)s->nstrips * p.ny, s->march_ns > 0 ? kMarchMoments[f] : m.march2) *
                (odd ? kOddF16 : 1.0) * (gamma ? 0.75 / 0.9 : 1.0);

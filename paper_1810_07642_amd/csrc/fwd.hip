@@ -49,7 +49,8 @@ __device__ __forceinline__ void init_field(const StepArgs &A, int x, int y, cons
     T *pr = (T *)A.kfield + 2 * ((size_t)y * A.ldx + x);
     pr[0] = (T)(-gm / 6.0);
     pr[1] = (T)(-gm) * kap;
-  }}
+  }
+}
 
 template <int P>
 __global__ void init_kernel(StepArgs A, const double *h0, const double *theta, const double *gamma, int field,

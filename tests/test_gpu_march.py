@@ -116,3 +116,25 @@ def test_captures_of_passes_of_moments_equal_single_steps_bitwise(prec, field, g
                 env["TFLBM_MARCH_ROWS"] = rows
             for a, b in zip(captures(make(prec, ny, nx, field, env, p)), ref):
                 assert torch.equal(a, b), (ny, nx, ns, rows)
+
+
+@pytest.mark.parametrize("field", [True, False])
+def test_fp64_two_step_passes_by_the_general_stages_bitwise(field):
+    """FP64 at tau = 1 on a lattice of three steps per pass: a call of two
+    steps, and the last pass of 5 and 8 without passes of moments, run the general
+    stages' two-step kernel.  The same bits as single steps, and as the general
+    stages throughout."""
+    p = dict(tau=1.0, gamma=0.01, g=1e-3, hstar=0.1, delta=1.0, ax=1e-5, ay=-1e-5)
+    for steps, env in ((2, {}), (5, {"TFLBM_MARCH": "0"}), (8, {"TFLBM_MARCH": "0"})):
+        banner(f"two-step passes by the general stages: field={field} {steps} steps")
+        got = [state(make("fp64", 1024, 1024, field, e, p), steps)
+               for e in (env, {"TFLBM_FUSE": "1"}, {"TFLBM_OMEGA1": "0"})]
+        for other in got[1:]:
+            for a, b in zip(got[0], other):
+                assert torch.equal(a, b), steps
+
+
+def state(sim, steps):
+    sim.step(steps)
+    sim.check()
+    return [sim.state_save().cpu()] + [t.cpu() for t in sim.read()]

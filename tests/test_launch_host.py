@@ -188,3 +188,12 @@ def test_captured_calls_split_into_passes_of_moments(exe, march, middle):
                 assert all("march_kernel" in l.kernel for l in r.launches) and len(r.launches) >= 4
             assert any(middle in l.kernel for r in res[-3:-1] for l in r.launches)
             assert not any("march_kernel" in l.kernel for l in res[-1].launches)
+
+
+def test_fp64_two_step_passes_take_the_general_stages(exe):
+    """On lattices of three steps per pass: calls of two steps, and without
+    passes of moments the last pass of a call of 5."""
+    res = lh.drive(exe, [lh.sim(1024, 1024, "fp64"), "step 2", "env TFLBM_MARCH 0", lh.sim(1024, 1024, "fp64"), "step 5"])
+    general, three = "11step_kernelILi0ELi1ELb0ELi2ELb0ELb0E", "11step_kernelILi0ELi1ELb0ELi3ELb0ELb1E"
+    assert [general in l.kernel for l in res[1].launches] == [True]
+    assert len(res[4].launches) == 2 and three in res[4].launches[0].kernel and general in res[4].launches[1].kernel
