@@ -455,15 +455,15 @@ static int launch_march_steps(tflbm_sim *sim, const MarchSplit &sp, void *d_capt
 // handle allows while that many remain, then shorter ones (with capture: the
 // moments of steps i .. i + ns - 1 of a pass, one capture block apart).
 static int launch_steps(tflbm_sim *sim, int64_t nsteps, void *d_capture, hipStream_t st) {
-  if (sim->block.ns > 0) {
-    const int64_t k = block_passes(sim, nsteps);
-    if (block_takes(sim, nsteps, k, d_capture != nullptr)) return launch_block_steps(sim, nsteps, k, d_capture, st);
-  }
-  const size_t cap_bytes = tflbm_capture_bytes(sim);
   const int ns_max = march_steps_per_pass(sim);
   MarchSplit sp;
-  if (sim->march_ns > 0 && split_march(nsteps, (nsteps + ns_max - 1) / ns_max, sim->march_ns, sp))
-    return launch_march_steps(sim, sp, d_capture, st);
+  const bool moments = sim->march_ns > 0 && split_march(nsteps, (nsteps + ns_max - 1) / ns_max, sim->march_ns, sp);
+  if (sim->block.ns > 0) {
+    const int64_t k = block_passes(sim, nsteps);
+    if (block_takes(sim, nsteps, k, d_capture != nullptr, moments)) return launch_block_steps(sim, nsteps, k, d_capture, st);
+  }
+  if (moments) return launch_march_steps(sim, sp, d_capture, st);
+  const size_t cap_bytes = tflbm_capture_bytes(sim);
   int64_t i = 0;
   while (i < nsteps) {
     const int ns = (int)(nsteps - i < ns_max ? nsteps - i : ns_max);

@@ -69,28 +69,30 @@ constexpr double kMarchMoments[3] = {0.28e-3, 0.385e-3, 0};
 // Largest lattice the model was fitted to.
 constexpr int64_t kBlockMaxSites = 1500000;
 // A call is taken where the model puts its own passes below this fraction of the
-// marching kernels' time: [FP64, FP32, FP16S][stages][two steps or less, an odd and an
-// even number below ten, ten and more].  What the model leaves out sets the lines, and
-// only where the tiles take more than one round of the GPU (FP32 general captures: more
-// than two), or at omega = 1 two steps write captures (1 otherwise).  At omega = 1 a call's first and last pass move
-// populations (us per step, marching / block: FP32 1165x1007 2 steps 16.6 / 22.1, 4
-// steps 15.9 / 18.6, 24 steps 13.6 / 13.3; FP64 723x817 2 steps 15.1 / 18.1, 24 steps
-// 10.6 / 10.2), but the marching kernels have no passes that suit short odd calls (FP64
-// 658x740 3 steps with captures 18.6 / 15.2).  Captures go out in parts of lines from
-// tiles of 52 columns and less (FP32 general 1232x911 without 17.9 / 16.4, with 19.1 /
-// 25.2; 1157x327 with 12.1 / 9.2).  The lines are drawn from 2500 calls of 2 to 32 steps
-// on 190 lattices where the model sees between 0.55 and the whole of the marching time.
+// marching kernels' time: [FP64, FP32, FP16S][stages][two steps or less; more, which the
+// marching kernels step on populations; less than ten by their passes of moments; ten
+// and more by those].  What the model leaves out sets the lines, and only where the
+// tiles take more than one round of the GPU (FP32 general captures: more than two), or at
+// omega = 1 two steps write captures (1 otherwise).  At omega = 1 a call's first and last
+// pass move populations (us per step, marching / block: FP32 1165x1007 2 steps 16.6 /
+// 22.1, 4 steps 15.9 / 18.6, 24 steps 13.6 / 13.3; FP64 723x817 2 steps 15.1 / 18.1, 24
+// steps 10.6 / 10.2), but the marching kernels have slow passes for short odd calls
+// (FP64 658x740 3 steps with captures 18.6 / 15.2, FP32 1111x876 9 steps 16.2 / 12.7).
+// Captures go out in parts of lines from tiles of 52 columns and less (FP32 general
+// 1232x911 without 17.9 / 16.4, with 19.1 / 25.2; 1157x327 with 12.1 / 9.2).  The lines
+// are drawn from 5000 calls of 2 to 32 steps on 250 lattices where the model sees between
+// 0.55 and the whole of the marching time.
 enum CallKind { kGeneral = 0, kGeneralCap = 1, kOmega1 = 2, kOmega1Cap = 3 };
 constexpr double kLimit[3][4][4] = {
-    {{1.00, 1.00, 1.00, 1.00}, {0.90, 0.90, 0.90, 0.90}, {0.76, 1.00, 0.82, 0.88}, {0.68, 1.00, 0.82, 0.92}},
-    {{0.95, 0.95, 0.95, 0.95}, {0.69, 0.69, 0.69, 0.69}, {0.70, 0.90, 0.78, 0.82}, {0.56, 0.85, 0.73, 0.82}},
-    {{1.00, 1.00, 1.00, 1.00}, {0.90, 0.90, 0.90, 0.90}, {0.84, 0.88, 0.86, 0.88}, {0.68, 0.86, 0.86, 0.88}}};
+    {{1.00, 1.00, 1.00, 1.00}, {0.90, 0.90, 0.90, 0.90}, {0.76, 1.20, 0.82, 0.89}, {0.68, 1.20, 0.90, 0.97}},
+    {{0.95, 0.95, 0.95, 0.95}, {0.69, 0.69, 0.69, 0.69}, {0.70, 0.95, 0.86, 0.84}, {0.56, 0.90, 0.85, 0.86}},
+    {{1.00, 1.00, 1.00, 1.00}, {0.90, 0.90, 0.90, 0.90}, {0.84, 0.89, 0.89, 0.89}, {0.68, 0.88, 0.88, 0.88}}};
 // Two or three steps that the number of passes makes single ones, in one round of
 // tiles: [form][general, omega = 1].  (FP32 at tau = 0.9 161x1164, two steps: 11.4 / 7.0;
 // measured from 0.58 to 1.02 of the marching kernel below these lines.)
 constexpr double kSingleLimit[3][2] = {{0.95, 0.70}, {0.97, 0.70}, {0.88, 0.70}};
-// And a plan is made where some call of many steps takes it.
-constexpr double kPlanLimit[3][2] = {{0.90, 0.92}, {0.90, 0.82}, {0.90, 0.88}};  // [form][general, omega = 1]
+// And a plan is made where some calls take it.
+constexpr double kPlanLimit[3][2] = {{0.90, 0.97}, {0.90, 0.95}, {0.90, 0.89}};  // [form][general, omega = 1]
 
 static const BlockShape *shapes_of(int prec, bool w1, int &n) {
   auto of = [&](const auto &list) {
@@ -141,11 +143,11 @@ bool plan_block(const tflbm_sim *s, BlockPlan &best) {
   return t < kPlanLimit[f][s->w1 && !gamma ? 1 : 0] * best.limit;
 }
 
-// Whether a call of nsteps steps takes the plan, in k passes: not where it is
-// modelled too slow, nor (odd widths of FP16S excepted) a call of one step, which the
-// marching kernel does for less than a tile's load and store (FP64 64^2 4.5 us against
-// 6.3 in a pass of one).
-bool block_takes(const tflbm_sim *s, int64_t nsteps, int64_t k, bool capture) {
+// Whether a call of nsteps steps takes the plan, in k passes (moments: the marching
+// kernels would hand over moments): not where it is modelled too slow, nor (odd widths of
+// FP16S excepted) a call of one step, which the marching kernel does for less than a
+// tile's load and store (FP64 64^2 4.5 us against 6.3 in a pass of one).
+bool block_takes(const tflbm_sim *s, int64_t nsteps, int64_t k, bool capture, bool moments) {
   const BlockPlan &b = s->block;
   if (b.ns == 0 || nsteps == 0 || (nsteps == 1 && !b.always)) return false;
   const tflbm_params &p = s->p;
@@ -154,9 +156,11 @@ bool block_takes(const tflbm_sim *s, int64_t nsteps, int64_t k, bool capture) {
   const BlockShape &sh = shapes_of(p.prec, s->w1, n)[b.shape];
   // (a surface tension field's calls hand over no moments by the marching kernels)
   const int kind = capture ? (s->w1 ? kOmega1Cap : kGeneralCap) : (s->w1 && s->kfield != kGammaKappa ? kOmega1 : kGeneral);
-  const int length = nsteps <= 2 ? 0 : (nsteps >= 10 ? 3 : ((nsteps & 1) ? 1 : 2));
+  const int length = nsteps <= 2 ? 0 : (!moments ? 1 : (nsteps < 10 ? 2 : 3));
   const int rounds = (Tiles(p.nx, p.ny, sh, (int)((nsteps + k - 1) / k), extra).ntiles + 255) / 256;
   double limit = kLimit[f][kind][length];
+  if (moments && (nsteps & 1)) limit += 0.05;  // one of their passes has three steps
+  if ((nsteps & 1) == 0 && limit > 1.0) limit = 1.0;
   if (k >= nsteps && !b.always) limit = rounds <= 1 ? kSingleLimit[f][s->w1 ? 1 : 0] : 0.0;
   else if (rounds <= 1 && !(kind == kOmega1Cap && length == 0)) limit = 1.0;
   else if (rounds == 2 && kind == kGeneralCap && p.prec == kF32) limit = kLimit[f][kGeneral][length];

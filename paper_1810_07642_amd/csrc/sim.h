@@ -81,7 +81,7 @@ void plan_launches(tflbm_sim *s);
 // whether a call of nsteps steps takes it, in k passes, and its launch shape for a
 // pass of ns steps.
 bool plan_block(const tflbm_sim *s, BlockPlan &best);
-bool block_takes(const tflbm_sim *s, int64_t nsteps, int64_t k, bool capture);
+bool block_takes(const tflbm_sim *s, int64_t nsteps, int64_t k, bool capture, bool moments);
 void shape_block(const tflbm_sim *s, int shape, int ns, BlockArgs &A);
 // The same for the reverse block kernel.
 bool plan_adj_block(const tflbm_sim *s, BlockPlan &best);

@@ -125,7 +125,8 @@ def test_fp64_two_step_passes_by_the_general_stages_bitwise(field):
     stages' two-step kernel.  The same bits as single steps, and as the general
     stages throughout."""
     p = dict(tau=1.0, gamma=0.01, g=1e-3, hstar=0.1, delta=1.0, ax=1e-5, ay=-1e-5)
-    for steps, env in ((2, {}), (5, {"TFLBM_MARCH": "0"}), (8, {"TFLBM_MARCH": "0"})):
+    for steps, env in ((2, {"TFLBM_BLOCK": "0"}), (5, {"TFLBM_BLOCK": "0", "TFLBM_MARCH": "0"}),
+                       (8, {"TFLBM_BLOCK": "0", "TFLBM_MARCH": "0"})):
         banner(f"two-step passes by the general stages: field={field} {steps} steps")
         got = [state(make("fp64", 1024, 1024, field, e, p), steps)
                for e in (env, {"TFLBM_FUSE": "1"}, {"TFLBM_OMEGA1": "0"})]

@@ -193,7 +193,8 @@ def test_captured_calls_split_into_passes_of_moments(exe, march, middle):
 def test_fp64_two_step_passes_take_the_general_stages(exe):
     """On lattices of three steps per pass: calls of two steps, and without
     passes of moments the last pass of a call of 5."""
-    res = lh.drive(exe, [lh.sim(1024, 1024, "fp64"), "step 2", "env TFLBM_MARCH 0", lh.sim(1024, 1024, "fp64"), "step 5"])
+    sim = lh.sim(1024, 1024, "fp64")
+    res = lh.drive(exe, ["env TFLBM_BLOCK 0", sim, "step 2", "env TFLBM_MARCH 0", sim, "step 5"])
     general, three = "11step_kernelILi0ELi1ELb0ELi2ELb0ELb0E", "11step_kernelILi0ELi1ELb0ELi3ELb0ELb1E"
-    assert [general in l.kernel for l in res[1].launches] == [True]
-    assert len(res[4].launches) == 2 and three in res[4].launches[0].kernel and general in res[4].launches[1].kernel
+    assert [general in l.kernel for l in res[2].launches] == [True]
+    assert len(res[5].launches) == 2 and three in res[5].launches[0].kernel and general in res[5].launches[1].kernel
